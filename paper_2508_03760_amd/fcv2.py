@@ -1,9 +1,12 @@
-"""Thin ctypes binding of the C-ABI library libfcv2 (include/fcv2.h).  Same names as the C entry points.
+"""Thin binding of the C-ABI library libfcv2 (include/fcv2.h).  Same names as the C entry points.
 
 Argument marshalling only: torch supplies device memory and the current HIP stream, every step of the codec
-runs in the library's kernels.  There is no CPU fallback: if the library cannot be loaded, calls raise.
+runs in the library's kernels.  The calls that launch kernels are marshalled by the native module _fcv2_torch
+(csrc/fcv2_torch.cpp: a decode-sized call spends less time on the GPU than Python needs to read its tensors); the host-only
+ones go through ctypes.  There is no CPU fallback: if the library or its binding cannot be loaded, calls raise.
 """
 import ctypes as C
+import importlib.util
 import os
 from dataclasses import dataclass
 
@@ -54,6 +57,7 @@ class Layout:
 
 
 _lib = None
+_native = None  # the module _fcv2_torch once it is loaded
 
 
 def lib():
@@ -90,6 +94,19 @@ def _check(rc, what):
         raise Fcv2Error(f"{what}: {lib().fcv2_status_string(rc).decode()} ({rc})")
 
 
+def _load_native():
+    """The native binding, loaded on first use (after libfcv2.so, which lib() compiles together with it if need be)."""
+    global _native
+    if _native is None:
+        lib()
+        spec = importlib.util.spec_from_file_location("_fcv2_torch", _build.BINDING)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.set_errors(Fcv2Error, torch.OutOfMemoryError)
+        _native = m
+    return _native
+
+
 def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
@@ -112,70 +129,23 @@ def get_layout(n, bits, group, flags, section_align=TENSOR_ALIGN) -> Layout:
 
 def quantize_pack(x: torch.Tensor, bits, group, flags, out: torch.Tensor = None) -> torch.Tensor:
     """x: bf16 device tensor (any shape, contiguous).  Returns the packed record as a uint8 device tensor."""
-    if x.dtype != torch.bfloat16:
-        raise Fcv2Error("x must be bfloat16")
-    n = x.numel()
-    L = get_layout(n, bits, group, flags)
-    if out is None:
-        out = torch.zeros(L.total_bytes, dtype=torch.uint8, device=x.device)
-    elif out.numel() < L.total_bytes or out.dtype != torch.uint8:
-        raise Fcv2Error("out must be a uint8 tensor of at least total_bytes")
-    _check(lib().fcv2_quantize_pack(_dev(x, "x"), n, C.byref(_Fmt(bits, group, flags)), _dev(out, "out"), _stream()),
-           "fcv2_quantize_pack")
-    return out
+    return (_native or _load_native()).quantize_pack(x, bits, group, flags, out)
 
 
 def unpack_dequant(packed: torch.Tensor, n, bits, group, flags, out_dtype=torch.float32,
                    out: torch.Tensor = None) -> torch.Tensor:
-    L = get_layout(n, bits, group, flags)
-    if packed.dtype != torch.uint8 or packed.numel() < L.total_bytes:
-        raise Fcv2Error("packed must be a uint8 tensor of at least total_bytes")
-    if out_dtype not in (torch.float32, torch.bfloat16):
-        raise Fcv2Error("out_dtype must be float32 or bfloat16")
-    if out is None:
-        out = torch.empty(n, dtype=out_dtype, device=packed.device)
-    elif out.numel() != n or out.dtype != out_dtype:
-        raise Fcv2Error("out has the wrong size or dtype")
-    _check(lib().fcv2_unpack_dequant(_dev(packed, "packed"), n, C.byref(_Fmt(bits, group, flags)), _dev(out, "out"),
-                                     DT_FP32 if out_dtype == torch.float32 else DT_BF16, _stream()),
-           "fcv2_unpack_dequant")
-    return out
+    return (_native or _load_native()).unpack_dequant(packed, n, bits, group, flags, out_dtype, out)
 
 
 def quantize_pack_slices(x: torch.Tensor, n_slices, bits, group, flags, out: torch.Tensor = None) -> torch.Tensor:
     """Cut x into n_slices equal slices and pack each into a record of its own.  Returns a uint8 tensor
     [n_slices, record_stride]; row j is the record of slice j."""
-    if x.dtype != torch.bfloat16:
-        raise Fcv2Error("x must be bfloat16")
-    n = x.numel()
-    if n_slices < 1 or n % n_slices:
-        raise Fcv2Error("n must be a multiple of n_slices")
-    L = get_layout(n // n_slices, bits, group, flags)
-    if out is None:
-        out = torch.zeros((n_slices, L.total_bytes), dtype=torch.uint8, device=x.device)
-    elif out.dtype != torch.uint8 or out.dim() != 2 or out.shape[0] != n_slices or out.shape[1] < L.total_bytes:
-        raise Fcv2Error("out must be a uint8 tensor [n_slices, >= total_bytes]")
-    _check(lib().fcv2_quantize_pack_slices(_dev(x, "x"), n, n_slices, C.byref(_Fmt(bits, group, flags)), _dev(out, "out"),
-                                           out.shape[1], _stream()), "fcv2_quantize_pack_slices")
-    return out
+    return (_native or _load_native()).quantize_pack_slices(x, n_slices, bits, group, flags, out)
 
 
 def unpack_dequant_slices(records, n, bits, group, flags, out_dtype=torch.float32, out: torch.Tensor = None) -> torch.Tensor:
     """records: list of packed uint8 device tensors, record j = slice j of the output of n elements."""
-    k = len(records)
-    if k < 1 or n % k:
-        raise Fcv2Error("n must be a multiple of the number of records")
-    L = get_layout(n // k, bits, group, flags)
-    for r in records:
-        if r.dtype != torch.uint8 or r.numel() < L.total_bytes:
-            raise Fcv2Error("every record must be a uint8 tensor of at least total_bytes")
-    if out is None:
-        out = torch.empty(n, dtype=out_dtype, device=records[0].device)
-    arr = (C.c_void_p * k)(*[_dev(r, "record").value for r in records])
-    _check(lib().fcv2_unpack_dequant_slices(arr, k, n, C.byref(_Fmt(bits, group, flags)), _dev(out, "out"),
-                                            DT_FP32 if out_dtype == torch.float32 else DT_BF16, _stream()),
-           "fcv2_unpack_dequant_slices")
-    return out
+    return (_native or _load_native()).unpack_dequant_slices(records, n, bits, group, flags, out_dtype, out)
 
 
 def stream_copy(src: torch.Tensor, dst: torch.Tensor):
@@ -190,23 +160,7 @@ def reduce_requant(peers, n, fmt_in, fmt_out=None, want_sum=False, out: torch.Te
                    sum_out: torch.Tensor = None):
     """peers: list of packed uint8 device tensors of format fmt_in = (bits, group, flags).
     Returns packed_out, or (packed_out, fp32 sums) with want_sum."""
-    fmt_out = fmt_out or fmt_in
-    Lin = get_layout(n, *fmt_in)
-    Lout = get_layout(n, *fmt_out)
-    if not 1 <= len(peers) <= MAX_PEERS:
-        raise Fcv2Error("1..16 peers")
-    for p in peers:
-        if p.dtype != torch.uint8 or p.numel() < Lin.total_bytes:
-            raise Fcv2Error("every peer must be a uint8 tensor of at least total_bytes")
-    if out is None:
-        out = torch.zeros(Lout.total_bytes, dtype=torch.uint8, device=peers[0].device)
-    if want_sum and sum_out is None:
-        sum_out = torch.empty(n, dtype=torch.float32, device=peers[0].device)
-    arr = (C.c_void_p * len(peers))(*[_dev(p, "peer").value for p in peers])
-    _check(lib().fcv2_reduce_requant(arr, len(peers), n, C.byref(_Fmt(*fmt_in)), C.byref(_Fmt(*fmt_out)),
-                                     _dev(out, "out"), _dev(sum_out, "sum_out") if sum_out is not None else None,
-                                     _stream()), "fcv2_reduce_requant")
-    return (out, sum_out) if want_sum else out
+    return (_native or _load_native()).reduce_requant(peers, n, fmt_in, fmt_out, want_sum, out, sum_out)
 
 
 def dispatch_workspace_bytes(T, K, E) -> int:
@@ -219,38 +173,11 @@ def dispatch_quant(x: torch.Tensor, topk_ids: torch.Tensor, E, bits, group, flag
                    expert_offsets=None, row_src=None, workspace=None):
     """x: [T, H] bf16, topk_ids: [T, K] int32 (device).  Returns send_buf [T*K, row_bytes] uint8,
     expert_offsets [E+1] int32, row_src [T*K] int32 (first expert_offsets[E] entries valid)."""
-    T, H = x.shape
-    K = topk_ids.shape[1]
-    if x.dtype != torch.bfloat16 or topk_ids.dtype != torch.int32 or topk_ids.shape[0] != T:
-        raise Fcv2Error("x must be [T,H] bfloat16 and topk_ids [T,K] int32")
-    L = get_layout(H, bits, group, flags, ROW_ALIGN)
-    dev = x.device
-    if send_buf is None:
-        send_buf = torch.zeros((T * K, L.total_bytes), dtype=torch.uint8, device=dev)
-    if expert_offsets is None:
-        expert_offsets = torch.zeros(E + 1, dtype=torch.int32, device=dev)
-    if row_src is None:
-        row_src = torch.full((T * K,), -1, dtype=torch.int32, device=dev)
-    need = dispatch_workspace_bytes(T, K, E)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    _check(lib().fcv2_dispatch_quant(_dev(x, "x"), _dev(topk_ids, "topk_ids"), T, H, K, E,
-                                     C.byref(_Fmt(bits, group, flags)), _dev(send_buf, "send_buf"),
-                                     _dev(expert_offsets, "expert_offsets"), _dev(row_src, "row_src"),
-                                     _dev(workspace, "workspace"), workspace.numel(), _stream()), "fcv2_dispatch_quant")
-    return send_buf, expert_offsets, row_src
+    return (_native or _load_native()).dispatch_quant(x, topk_ids, E, bits, group, flags, send_buf, expert_offsets, row_src, workspace)
 
 
 def dispatch_quant_noalloc(x: torch.Tensor, topk_ids: torch.Tensor, E, bits, group, flags, send_buf: torch.Tensor,
                            expert_offsets: torch.Tensor, row_src: torch.Tensor):
     """fcv2_dispatch_quant_noalloc: as dispatch_quant, but the planning scratch is the library's static device array.
     The caller passes every output; this binding allocates nothing either."""
-    T, H = x.shape
-    K = topk_ids.shape[1]
-    if x.dtype != torch.bfloat16 or topk_ids.dtype != torch.int32 or topk_ids.shape[0] != T:
-        raise Fcv2Error("x must be [T,H] bfloat16 and topk_ids [T,K] int32")
-    _check(lib().fcv2_dispatch_quant_noalloc(_dev(x, "x"), _dev(topk_ids, "topk_ids"), T, H, K, E,
-                                             C.byref(_Fmt(bits, group, flags)), _dev(send_buf, "send_buf"),
-                                             _dev(expert_offsets, "expert_offsets"), _dev(row_src, "row_src"), _stream()),
-           "fcv2_dispatch_quant_noalloc")
-    return send_buf, expert_offsets, row_src
+    return (_native or _load_native()).dispatch_quant_noalloc(x, topk_ids, E, bits, group, flags, send_buf, expert_offsets, row_src)
