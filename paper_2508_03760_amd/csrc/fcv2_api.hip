@@ -1,5 +1,6 @@
 // fcv2_api.hip -- the C ABI of libfcv2 (include/fcv2.h): argument checks and layout on the host, then the launch
 // function of the call.  Also the plain copy kernel used as a bandwidth yardstick.
+#include "fcv2_fresh.h"
 #include "fcv2_host.h"
 
 namespace fcv2 {
@@ -43,7 +44,7 @@ static const uint64_t kMaxElems = 1ull << 31;
 // Argument checks and launch of the dispatch call; serves both entry points (workspace from the caller, or the
 // library's static scratch).
 int dispatch_checked(const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E, const fcv2_fmt_t* fmt, void* send,
-                     int32_t* expert_offsets, int32_t* row_src, void* ws, size_t ws_bytes, void* stream) {
+                     int32_t* expert_offsets, int32_t* row_src, void* ws, size_t ws_bytes, bool fresh, void* stream) {
     if (!x || !ids || !fmt || !send || !expert_offsets || !row_src || !ws) return FCV2_ERR_INVALID_ARG;
     size_t need = 0;
     int rc = fcv2_dispatch_workspace_bytes(T, K, E, &need);
@@ -60,7 +61,7 @@ int dispatch_checked(const void* x, const int32_t* ids, uint32_t T, uint32_t H, 
         ((uintptr_t)row_src & 3u))
         return FCV2_ERR_ALIGN;
     return launch_dispatch(fmt, x, ids, T, H, K, E, (uint8_t*)send, expert_offsets, row_src, ws, rec_of(l, fmt), (uint32_t)l.total_bytes,
-                           (hipStream_t)stream);
+                           fresh, (hipStream_t)stream);
 }
 
 }  // namespace fcv2
@@ -127,15 +128,31 @@ static int check_slices(uint64_t n, uint32_t n_slices, const fcv2_fmt_t* fmt, fc
     return FCV2_OK;
 }
 
-int fcv2_quantize_pack_slices(const void* x, uint64_t n, uint32_t n_slices, const fcv2_fmt_t* fmt, void* packed,
-                              uint64_t record_stride, void* stream) {
+// Whether a record has padding at all: sizes that fill whole sections need none.
+static bool has_padding(const fcv2_layout_t& l, const fcv2_fmt_t* f) {
+    const uint64_t meta = (f->flags & FCV2_F_META_FP32) ? 4 : (f->flags & FCV2_F_META_INT) ? 1 : 2;
+    const uint64_t spikes = (f->flags & FCV2_F_SPIKE) ? ((f->flags & FCV2_F_IDX_BF16) ? 8 : 6) : 0;
+    return l.n / 8 * f->bits + l.n_groups * (2 * meta + spikes) != l.total_bytes;
+}
+
+static int quantize_slices(const void* x, uint64_t n, uint32_t n_slices, const fcv2_fmt_t* fmt, void* packed, uint64_t record_stride, bool fresh,
+                           void* stream) {
     if (!x || !packed || !fmt) return FCV2_ERR_INVALID_ARG;
     fcv2_layout_t l;
     int rc = check_slices(n, n_slices, fmt, &l);
     if (rc != FCV2_OK) return rc;
+    if (fresh) record_stride = l.total_bytes;
     if (n_slices > 1 && (record_stride < l.total_bytes || record_stride % FCV2_TENSOR_ALIGN != 0)) return FCV2_ERR_INVALID_ARG;
     if (!aligned16(x) || !aligned16(packed)) return FCV2_ERR_ALIGN;
-    return launch_quantize(fmt, x, n, packed, rec_of(l, fmt), n_slices, record_stride, (hipStream_t)stream);
+    return launch_quantize(fmt, x, n, packed, rec_of(l, fmt), n_slices, record_stride, fresh && has_padding(l, fmt), (hipStream_t)stream);
+}
+
+int fcv2_quantize_pack_slices(const void* x, uint64_t n, uint32_t n_slices, const fcv2_fmt_t* fmt, void* packed,
+                              uint64_t record_stride, void* stream) {
+    return quantize_slices(x, n, n_slices, fmt, packed, record_stride, false, stream);
+}
+int fcv2_quantize_pack_slices_fresh(const void* x, uint64_t n, uint32_t n_slices, const fcv2_fmt_t* fmt, void* packed, void* stream) {
+    return quantize_slices(x, n, n_slices, fmt, packed, 0, true, stream);
 }
 
 int fcv2_quantize_pack(const void* x, uint64_t n, const fcv2_fmt_t* fmt, void* packed, void* stream) {
@@ -166,8 +183,8 @@ int fcv2_unpack_dequant(const void* packed, uint64_t n, const fcv2_fmt_t* fmt, v
     return fcv2_unpack_dequant_slices(one, 1, n, fmt, out, out_dtype, stream);
 }
 
-int fcv2_reduce_requant(const void* const* peers, int n_peers, uint64_t n, const fcv2_fmt_t* fmt_in, const fcv2_fmt_t* fmt_out,
-                        void* packed_out, float* sum_out, void* stream) {
+static int reduce(const void* const* peers, int n_peers, uint64_t n, const fcv2_fmt_t* fmt_in, const fcv2_fmt_t* fmt_out, void* packed_out,
+                  float* sum_out, bool fresh, void* stream) {
     if (!peers || !fmt_in || !fmt_out || !packed_out) return FCV2_ERR_INVALID_ARG;
     if (n_peers < 1 || n_peers > FCV2_MAX_PEERS) return FCV2_ERR_INVALID_ARG;
     fcv2_layout_t lin, lout;
@@ -186,7 +203,17 @@ int fcv2_reduce_requant(const void* const* peers, int n_peers, uint64_t n, const
         if (!aligned16(ptr)) return FCV2_ERR_ALIGN;
         pp.base[p] = (const uint8_t*)ptr;
     }
-    return launch_reduce(fmt_in, fmt_out, pp, n_peers, n, rec_of(lin, fmt_in), packed_out, rec_of(lout, fmt_out), sum_out, (hipStream_t)stream);
+    return launch_reduce(fmt_in, fmt_out, pp, n_peers, n, rec_of(lin, fmt_in), packed_out, rec_of(lout, fmt_out), sum_out,
+                         fresh && has_padding(lout, fmt_out), (hipStream_t)stream);
+}
+
+int fcv2_reduce_requant(const void* const* peers, int n_peers, uint64_t n, const fcv2_fmt_t* fmt_in, const fcv2_fmt_t* fmt_out,
+                        void* packed_out, float* sum_out, void* stream) {
+    return reduce(peers, n_peers, n, fmt_in, fmt_out, packed_out, sum_out, false, stream);
+}
+int fcv2_reduce_requant_fresh(const void* const* peers, int n_peers, uint64_t n, const fcv2_fmt_t* fmt_in, const fcv2_fmt_t* fmt_out,
+                              void* packed_out, float* sum_out, void* stream) {
+    return reduce(peers, n_peers, n, fmt_in, fmt_out, packed_out, sum_out, true, stream);
 }
 
 int fcv2_dispatch_workspace_bytes(uint32_t T, uint32_t K, uint32_t E, size_t* out) {
@@ -199,7 +226,11 @@ int fcv2_dispatch_workspace_bytes(uint32_t T, uint32_t K, uint32_t E, size_t* ou
 
 int fcv2_dispatch_quant(const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E, const fcv2_fmt_t* fmt,
                         void* send, int32_t* expert_offsets, int32_t* row_src, void* ws, size_t ws_bytes, void* stream) {
-    return fcv2::dispatch_checked(x, ids, T, H, K, E, fmt, send, expert_offsets, row_src, ws, ws_bytes, stream);
+    return fcv2::dispatch_checked(x, ids, T, H, K, E, fmt, send, expert_offsets, row_src, ws, ws_bytes, false, stream);
+}
+int fcv2_dispatch_quant_fresh(const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E, const fcv2_fmt_t* fmt,
+                              void* send, int32_t* expert_offsets, int32_t* row_src, void* ws, size_t ws_bytes, void* stream) {
+    return fcv2::dispatch_checked(x, ids, T, H, K, E, fmt, send, expert_offsets, row_src, ws, ws_bytes, true, stream);
 }
 
 int fcv2_stream_copy(const void* src, void* dst, uint64_t bytes, void* stream) {

@@ -48,6 +48,8 @@ struct GroupMeta {
 
 // How scale and zero are stored.
 constexpr uint32_t kMetaBf16 = 0, kMetaFp32 = 1, kMetaInt = 2;
+// Added to the metadata mode of an output: the padding between the record's sections is written as zero.
+constexpr uint32_t kZeroPadding = 4;
 
 // Integer metadata: per-block LDS tables of 2^(k/10) and of the decision points of Eq. 1, one entry per code, so
 // that coding and decoding a scale are table reads.  Called by all threads of a 256-thread block, before any of
@@ -413,6 +415,29 @@ template <bool SR> __device__ __forceinline__ void store_meta(uint8_t* base, con
         else
             *reinterpret_cast<uint16_t*>(base + (r.spike_idx + 2u * g)) = (uint16_t)m.si;
     }
+}
+
+// Zeroes the padding behind every section of a record of n elements (ng groups), by the 64 lanes of one wave: a section ends
+// less than 256 bytes before the next begins.
+template <int BITS, bool SR> __device__ __forceinline__ void zero_padding(uint8_t* base, const Rec& r, uint32_t n, uint32_t ng, uint32_t mode,
+                                                                          uint32_t lane) {
+    using P = Planes<BITS>;
+    uint32_t end = 0;  // of the section before
+    auto section = [&](bool present, uint32_t at, uint32_t bytes) {
+        if (!present) return;
+        for (uint32_t b = end + lane; b < at; b += 64) base[b] = 0;
+        end = at + bytes;
+    };
+    section(P::w8, r.plane8, n);
+    section(P::w4, r.plane4, n / 2);
+    section(P::w2, r.plane2, n / 4);
+    section(P::w1, r.plane1, n / 8);
+    const uint32_t msz = (mode == kMetaFp32) ? 4u : (mode == kMetaInt) ? 1u : 2u;
+    section(true, r.scale, msz * ng);
+    section(true, r.zero, msz * ng);
+    section(SR, r.spike_val, 4u * ng);
+    section(SR, r.spike_idx, (r.idx_bf16 ? 4u : 2u) * ng);
+    section(true, r.total, 0u);
 }
 
 // ---- decoder core ------------------------------------------------------------------------------------------------

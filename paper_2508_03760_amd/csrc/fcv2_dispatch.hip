@@ -188,7 +188,7 @@ __device__ __forceinline__ int32_t dest_row_of(uint32_t i, const int32_t* __rest
 __global__ __launch_bounds__(kChunk) void k_dispatch_dest(const int32_t* __restrict__ ids, uint32_t n_slots, uint32_t E,
                                                           const int32_t* __restrict__ hist, const int32_t* __restrict__ totals,
                                                           const uint8_t* __restrict__ lrank, int32_t* __restrict__ expert_offsets,
-                                                          int32_t* __restrict__ dest, int32_t* __restrict__ row_src) {
+                                                          int32_t* __restrict__ dest, int32_t* __restrict__ row_src, uint32_t fresh) {
     extern __shared__ int32_t start[];  // [E]
     __shared__ int32_t lds8[8];
     const int32_t total = expert_starts_scan(expert_starts_read(totals, E), totals, start, lds8);
@@ -201,6 +201,7 @@ __global__ __launch_bounds__(kChunk) void k_dispatch_dest(const int32_t* __restr
         const int32_t r = dest_row_of(i, ids, E, hist, lrank, start);
         dest[i] = r;
         if (r >= 0) row_src[r] = (int32_t)i;
+        if (fresh && i >= (uint32_t)total) row_src[i] = -1;
     }
 }
 
@@ -292,6 +293,7 @@ struct DispatchPlan {  // what the planning launches left in the workspace, and 
     int32_t* expert_offsets;
     int32_t* row_src;
     uint32_t E;
+    uint32_t fresh_rows;  // T * K when send buffer and row_src hold no values yet (fcv2_fresh.h), else 0
 };
 
 template <int BITS, int LPG, bool SR, bool INT_META>
@@ -363,6 +365,7 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
                 run += plan.totals[e];
             }
         }
+        if (lane == 63) start[plan.E] = inc;
         if (blockIdx.x == 0 && lane == 63) plan.expert_offsets[plan.E] = inc;  // the last lane's inclusive sum: all routed copies
     }
     // the padding between a record's sections travels with the copies: it is written as zero
@@ -424,6 +427,17 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
             else store_stream(at, v);
         }
     }
+    // Rows that no routed copy takes (dropped slots leave them at the end), one per wave at a time over the whole grid.
+    for (uint32_t r = (uint32_t)start[plan.E] + blockIdx.x * n_waves + wave; r < plan.fresh_rows; r += gridDim.x * n_waves) {
+        uint4* at = reinterpret_cast<uint4*>(send + __umul24(r, row_bytes));
+        for (uint32_t p = lane; p < row_pieces; p += 64) at[p] = make_uint4(0, 0, 0, 0);
+        if (lane == 0) plan.row_src[r] = -1;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_dispatch_clear(uint4* __restrict__ send, uint32_t n16) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < n16) store_stream(&send[i], make_uint4(0, 0, 0, 0));
 }
 
 // Direct kernel: one wave tile = 2048 consecutive elements of x, every lane stores its share of the K copies itself.
@@ -483,8 +497,12 @@ template <int BITS, int G, bool SR> struct LaunchDispatch {
         // Row shapes the staged kernel cannot take: destination rows written out by one more small launch, then the direct kernel.
         const uint32_t n_slots = T * K;
         if (launch(k_dispatch_dest, dim3((n_slots + kChunk - 1) / kChunk), dim3(kChunk), plan.E * 4, st, plan.ids, n_slots, plan.E, plan.hist,
-                   plan.totals, plan.lrank, plan.expert_offsets, dest, plan.row_src) != FCV2_OK)
+                   plan.totals, plan.lrank, plan.expert_offsets, dest, plan.row_src, plan.fresh_rows) != FCV2_OK)
             return FCV2_ERR_LAUNCH;
+        if (plan.fresh_rows) {  // the direct kernel leaves the padding inside rows alone: clear everything first
+            const uint32_t n16 = (uint32_t)((uint64_t)n_slots * row_bytes / 16);
+            if (launch(k_dispatch_clear, dim3((n16 + kBlock - 1) / kBlock), dim3(kBlock), 0, st, (uint4*)send, n16) != FCV2_OK) return FCV2_ERR_LAUNCH;
+        }
         const dim3 grid(grid_lanes(n_lanes)), block(kBlock);
         if (im)
             return launch(k_dispatch_quant_t<BITS, LPG, SR, true>, grid, block, 0, st, (const uint4*)x, n_lanes, lpr, K, (const int32_t*)dest,
@@ -496,7 +514,7 @@ template <int BITS, int G, bool SR> struct LaunchDispatch {
 
 int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E,
                     uint8_t* send, int32_t* expert_offsets, int32_t* row_src, void* ws, const Rec& rec, uint32_t row_bytes,
-                    hipStream_t st) {
+                    bool fresh, hipStream_t st) {
     const DispatchWs w = dispatch_ws(T, K, E);
     int32_t* hist = (int32_t*)((uint8_t*)ws + w.off_hist);
     int32_t* totals = (int32_t*)((uint8_t*)ws + w.off_totals);
@@ -508,7 +526,7 @@ int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, ui
                        : launch(k_dispatch_count_rank<false>, dim3(w.n_chunks), dim3(kChunk), mask_bytes / 2, st, ids, w.n_slots, E, hist, lrank);
     if (rc != FCV2_OK) return FCV2_ERR_LAUNCH;
     if (launch(k_dispatch_scan_chunks, dim3(E), dim3(64), 0, st, hist, w.n_chunks, E, totals) != FCV2_OK) return FCV2_ERR_LAUNCH;
-    const DispatchPlan plan = {ids, hist, totals, lrank, expert_offsets, row_src, E};
+    const DispatchPlan plan = {ids, hist, totals, lrank, expert_offsets, row_src, E, fresh ? w.n_slots : 0u};
     return by_format<LaunchDispatch>(fmt, x, T, H, K, plan, dest, send, rec, row_bytes, meta_mode_of(fmt), st);
 }
 
@@ -550,6 +568,6 @@ extern "C" int fcv2_dispatch_quant_noalloc(const void* x, const int32_t* ids, ui
     if (!ws) return FCV2_ERR_LAUNCH;
     // Nothing in the scratch has to start at zero: the counting kernel writes every histogram entry of every chunk, the
     // scan every total, the rank kernel every destination slot, before any of them is read.
-    return fcv2::dispatch_checked(x, ids, T, H, K, E, fmt, send, expert_offsets, row_src, ws, FCV2_STATIC_SCRATCH_BYTES, stream);
+    return fcv2::dispatch_checked(x, ids, T, H, K, E, fmt, send, expert_offsets, row_src, ws, FCV2_STATIC_SCRATCH_BYTES, false, stream);
 }
 

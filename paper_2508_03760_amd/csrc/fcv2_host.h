@@ -81,19 +81,20 @@ static DispatchWs dispatch_ws(uint32_t T, uint32_t K, uint32_t E) {
     return w;
 }
 
-// One function per call, defined next to its kernels.  Arguments are checked by the C ABI functions before.
+// One function per call, defined next to its kernels.  Arguments are checked by the C ABI functions before.  zero_pad: the
+// padding of the packed output is written as zero too; fresh: likewise for everything in the dispatch outputs (fcv2_fresh.h).
 int launch_quantize(const fcv2_fmt_t* fmt, const void* x, uint64_t n, void* out, const Rec& rec, uint32_t n_slices,
-                    uint64_t record_stride, hipStream_t st);
+                    uint64_t record_stride, bool zero_pad, hipStream_t st);
 int launch_unpack(const fcv2_fmt_t* fmt, const PeerPtrs& records, uint32_t n_slices, const Rec& rec, uint64_t n, void* out,
                   uint32_t out_fp32, hipStream_t st);
 int launch_reduce(const fcv2_fmt_t* fmt_in, const fcv2_fmt_t* fmt_out, const PeerPtrs& peers, int n_peers, uint64_t n,
-                  const Rec& rec_in, void* out, const Rec& rec_out, float* sum_out, hipStream_t st);
+                  const Rec& rec_in, void* out, const Rec& rec_out, float* sum_out, bool zero_pad, hipStream_t st);
 int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E,
                     uint8_t* send, int32_t* expert_offsets, int32_t* row_src, void* ws, const Rec& rec, uint32_t row_bytes,
-                    hipStream_t st);
+                    bool fresh, hipStream_t st);
 
 // The checked dispatch call behind both C entry points (defined with the C ABI).
 int dispatch_checked(const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E, const fcv2_fmt_t* fmt, void* send,
-                     int32_t* expert_offsets, int32_t* row_src, void* ws, size_t ws_bytes, void* stream);
+                     int32_t* expert_offsets, int32_t* row_src, void* ws, size_t ws_bytes, bool fresh, void* stream);
 
 }  // namespace fcv2

@@ -12,7 +12,7 @@ __global__ __launch_bounds__(kBlock) void k_quantize_pack_t(const uint4* __restr
                                                             uint64_t record_stride) {
     // The integer metadata path is a compile-time variant here: its tables and extra live values would otherwise
     // cost the float formats a third of their registers (and with them two waves per SIMD).
-    const uint32_t meta_mode = INT_META ? kMetaInt : (meta_mode_arg == kMetaFp32 ? kMetaFp32 : kMetaBf16);
+    const uint32_t meta_mode = INT_META ? kMetaInt : ((meta_mode_arg & 3u) == kMetaFp32 ? kMetaFp32 : kMetaBf16);
     // The tensor may be cut into equal slices, each packed into a record of its own (records `record_stride` bytes
     // apart); slice_lanes is a multiple of 64 then, so a wave's tile lies in one slice.  One slice: slice_lanes = n_lanes.
     constexpr int EPL = kEplStream;
@@ -30,6 +30,8 @@ __global__ __launch_bounds__(kBlock) void k_quantize_pack_t(const uint4* __restr
     uint32_t w[16];
     tile_transpose(t, lds[wave], lane, w);
     const uint32_t slice = (tile * 64) / slice_lanes;  // uniform
+    if ((meta_mode_arg & kZeroPadding) && tile * 64 == slice * slice_lanes)  // the wave of a record's first tile
+        zero_padding<BITS, SR>(out + slice * record_stride, rec, slice_lanes * EPL, slice_lanes / LPG, meta_mode, lane);
     const uint32_t L = tile * 64 + lane;
     if (L < n_lanes) {  // groups never straddle the end: whole groups are in or out together
         uint32_t c[EPL / 4];
@@ -72,7 +74,7 @@ template <int BITS, int G, bool SR> struct LaunchQuantize {
         const uint32_t n_lanes = (uint32_t)(n / EPL);
         const uint32_t n_tiles = (n_lanes + 63) / 64;
         const QuantizeLaunch q = quantize_launch_shape(n_tiles, BITS);
-        if (meta_mode == kMetaInt)
+        if ((meta_mode & 3u) == kMetaInt)
             return launch(k_quantize_pack_t<BITS, G / EPL, SR, true>, dim3(q.blocks), dim3(kBlock), q.lds_pad, st,
                           (const uint4*)x, n_lanes, (uint8_t*)out, rec, meta_mode, n_lanes / n_slices, record_stride);
         return launch(k_quantize_pack_t<BITS, G / EPL, SR, false>, dim3(q.blocks), dim3(kBlock), q.lds_pad, st,
@@ -80,8 +82,8 @@ template <int BITS, int G, bool SR> struct LaunchQuantize {
     }
 };
 int launch_quantize(const fcv2_fmt_t* fmt, const void* x, uint64_t n, void* out, const Rec& rec, uint32_t n_slices,
-                    uint64_t record_stride, hipStream_t st) {
-    return by_format<LaunchQuantize>(fmt, x, n, out, rec, meta_mode_of(fmt), n_slices, record_stride, st);
+                    uint64_t record_stride, bool zero_pad, hipStream_t st) {
+    return by_format<LaunchQuantize>(fmt, x, n, out, rec, meta_mode_of(fmt) | (zero_pad ? kZeroPadding : 0u), n_slices, record_stride, st);
 }
 
 }  // namespace fcv2

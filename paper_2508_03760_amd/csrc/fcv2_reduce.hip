@@ -195,13 +195,15 @@ template <int BITS, int EPL, int LPG, bool SR, int PATCH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EPL == 32 ? FCV2_REDUCE_WAVES32 : FCV2_REDUCE_WAVES16)))
 void k_reduce_requant(PeerPtrs peers, int n_peers, uint32_t n_lanes, Rec rec_in,
                                                            uint8_t* __restrict__ out, Rec rec_out, float* __restrict__ sum_out,
-                                                           uint32_t meta_mode_in, uint32_t meta_mode_out) {
+                                                           uint32_t meta_mode_in, uint32_t meta_mode_out_arg) {
+    const uint32_t meta_mode_out = meta_mode_out_arg & 3u;
     constexpr int CH = FCV2_REDUCE_CH;  // peers in flight
     constexpr int ROW = 16 / 4 + 1;  // uint4 per private row of 16 dwords, one of padding: conflict-free 16-byte accesses
     __shared__ uint4 lds[kBlock * ROW];  // 20 KiB: eight blocks fill the 160 KiB of a compute unit exactly
     extern __shared__ float tabs[];      // the scale tables of the integer metadata: dynamic, present only when a format uses them
     if (meta_mode_in == kMetaInt || meta_mode_out == kMetaInt) fill_scale_tables(tabs);
     const uint32_t L = xcd_tile_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    if ((meta_mode_out_arg & kZeroPadding) && L < 64) zero_padding<BITS, SR>(out, rec_out, n_lanes * EPL, n_lanes / LPG, meta_mode_out, L);
     if (L >= n_lanes) return;
     const uint32_t lig = threadIdx.x & (LPG - 1);
     uint4* row = &lds[threadIdx.x * ROW];
@@ -270,12 +272,15 @@ template <int BITS_OUT, int EPL, int LPG, bool SR>
 __global__ __launch_bounds__(kBlock) void k_reduce_requant_mixed(PeerPtrs peers, int n_peers, uint32_t bits_in, uint32_t n_lanes,
                                                                  Rec rec_in, uint8_t* __restrict__ out, Rec rec_out,
                                                                  float* __restrict__ sum_out, uint32_t meta_mode_in,
-                                                                 uint32_t meta_mode_out) {
+                                                                 uint32_t meta_mode_out_arg) {
+    const uint32_t meta_mode_out = meta_mode_out_arg & 3u;
     constexpr int ROW = 16 / 4 + 1;
     __shared__ uint4 lds[kBlock * ROW];
     __shared__ float tabs[kScaleTables];
     if (meta_mode_in == kMetaInt || meta_mode_out == kMetaInt) fill_scale_tables(tabs);
     const uint32_t L = xcd_tile_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    if ((meta_mode_out_arg & kZeroPadding) && L < 64)
+        zero_padding<BITS_OUT, SR>(out, rec_out, n_lanes * EPL, n_lanes / LPG, meta_mode_out, L);
     if (L >= n_lanes) return;
     const uint32_t lig = threadIdx.x & (LPG - 1);
     uint4* row = &lds[threadIdx.x * ROW];
@@ -337,7 +342,7 @@ template <int BITS, int G, bool SR> struct LaunchReduce {
         constexpr int EPL = FCV2_REDUCE_EPL(G);
         constexpr int PATCH = FCV2_REDUCE_PATCH(BITS);
         const uint32_t n_lanes = (uint32_t)(n / EPL);
-        const size_t tab_bytes = (mf_in == kMetaInt || mf_out == kMetaInt) ? sizeof(float) * kScaleTables : 0;
+        const size_t tab_bytes = (mf_in == kMetaInt || (mf_out & 3u) == kMetaInt) ? sizeof(float) * kScaleTables : 0;
         return launch(k_reduce_requant<BITS, EPL, G / EPL, SR, PATCH>, dim3(grid_lanes_xcd(n_lanes)), dim3(kBlock), tab_bytes, st, peers,
                       n_peers, n_lanes, rec_in, (uint8_t*)out, rec_out, sum_out, mf_in, mf_out);
     }
@@ -352,8 +357,8 @@ template <int BITS, int G, bool SR> struct LaunchReduceMixed {  // BITS = output
     }
 };
 int launch_reduce(const fcv2_fmt_t* fmt_in, const fcv2_fmt_t* fmt_out, const PeerPtrs& peers, int n_peers, uint64_t n,
-                  const Rec& rec_in, void* out, const Rec& rec_out, float* sum_out, hipStream_t st) {
-    const uint32_t mf_in = meta_mode_of(fmt_in), mf_out = meta_mode_of(fmt_out);
+                  const Rec& rec_in, void* out, const Rec& rec_out, float* sum_out, bool zero_pad, hipStream_t st) {
+    const uint32_t mf_in = meta_mode_of(fmt_in), mf_out = meta_mode_of(fmt_out) | (zero_pad ? kZeroPadding : 0u);
     if (fmt_in->bits != fmt_out->bits)
         return by_format<LaunchReduceMixed>(fmt_out, peers, n_peers, fmt_in->bits, n, rec_in, out, rec_out, sum_out, mf_in, mf_out, st);
     return by_format<LaunchReduce>(fmt_in, peers, n_peers, n, rec_in, out, rec_out, sum_out, mf_in, mf_out, st);

@@ -16,6 +16,7 @@
 #include <string>
 
 #include "../../include/fcv2.h"
+#include "fcv2_fresh.h"
 
 namespace {
 
@@ -127,7 +128,6 @@ at::Tensor new_tensor(at::IntArrayRef shape, at::ScalarType t, const at::Tensor&
     return like.is_cuda() ? at::Tensor(at::detail::empty_cuda(shape, t, like.device(), std::nullopt))
                           : at::empty(shape, at::TensorOptions().dtype(t).device(like.device()));
 }
-at::Tensor new_zeros(at::IntArrayRef shape, at::ScalarType t, const at::Tensor& like) { return new_tensor(shape, t, like).zero_(); }
 
 // An optional argument that the caller may have passed: the tensor and the object to hand back.
 struct Given {
@@ -158,12 +158,14 @@ PyObject* quantize_pack(PyObject* const* a) {
     const fcv2_layout_t l = layout(n, f, FCV2_TENSOR_ALIGN);
     Given out(a[4]);
     if (!out)
-        out.made = new_zeros({(int64_t)l.total_bytes}, at::kByte, x);
+        out.made = new_tensor({(int64_t)l.total_bytes}, at::kByte, x);
     else if ((uint64_t)out.get("out").numel() < l.total_bytes || out.get("out").scalar_type() != at::kByte)
         fail("out must be a uint8 tensor of at least total_bytes");
     const void* xp = dev(x, "x");
     void *op = dev(out.get("out"), "out"), *st = stream();
-    check(without_gil([&] { return fcv2_quantize_pack(xp, n, &f, op, st); }), "fcv2_quantize_pack");
+    const bool fresh = !out;
+    check(without_gil([&] { return fresh ? fcv2_quantize_pack_slices_fresh(xp, n, 1, &f, op, st) : fcv2_quantize_pack(xp, n, &f, op, st); }),
+          "fcv2_quantize_pack");
     return out.result();
 }
 
@@ -199,7 +201,7 @@ PyObject* quantize_pack_slices(PyObject* const* a) {
     const fcv2_layout_t l = layout(n / (uint64_t)k, f, FCV2_TENSOR_ALIGN);
     Given out(a[5]);
     if (!out) {
-        out.made = new_zeros({k, (int64_t)l.total_bytes}, at::kByte, x);
+        out.made = new_tensor({k, (int64_t)l.total_bytes}, at::kByte, x);
     } else {
         const at::Tensor& o = out.get("out");
         if (o.scalar_type() != at::kByte || o.dim() != 2 || o.size(0) != k || (uint64_t)o.size(1) < l.total_bytes)
@@ -208,7 +210,12 @@ PyObject* quantize_pack_slices(PyObject* const* a) {
     const void* xp = dev(x, "x");
     const uint64_t stride = (uint64_t)out.get("out").size(1);
     void *op = dev(out.get("out"), "out"), *st = stream();
-    check(without_gil([&] { return fcv2_quantize_pack_slices(xp, n, (uint32_t)k, &f, op, stride, st); }), "fcv2_quantize_pack_slices");
+    const bool fresh = !out;
+    check(without_gil([&] {
+              return fresh ? fcv2_quantize_pack_slices_fresh(xp, n, (uint32_t)k, &f, op, st)
+                           : fcv2_quantize_pack_slices(xp, n, (uint32_t)k, &f, op, stride, st);
+          }),
+          "fcv2_quantize_pack_slices");
     return out.result();
 }
 
@@ -244,14 +251,15 @@ PyObject* reduce_requant(PyObject* const* a) {
     if (peers.n < 1 || peers.n > FCV2_MAX_PEERS) fail("1..16 peers");
     peers.check_sizes(lin.total_bytes, "peer", "every peer must be a uint8 tensor of at least total_bytes");
     Given out(a[5]), sum(a[6]);
-    if (!out) out.made = new_zeros({(int64_t)lout.total_bytes}, at::kByte, peers.at(0, "peer"));
+    if (!out) out.made = new_tensor({(int64_t)lout.total_bytes}, at::kByte, peers.at(0, "peer"));
     if (want && !sum) sum.made = new_tensor({(int64_t)n}, at::kFloat, peers.at(0, "peer"));
     const void* p[FCV2_MAX_PEERS];
     peers.pointers(p, "peer");
     void* op = dev(out.get("out"), "out");
     float* sp = (sum || want) ? (float*)dev(sum.get("sum_out"), "sum_out") : nullptr;
     void* st = stream();
-    check(without_gil([&] { return fcv2_reduce_requant(p, peers.n, n, &fin, &fout, op, sp, st); }), "fcv2_reduce_requant");
+    const auto call = out ? fcv2_reduce_requant : fcv2_reduce_requant_fresh;
+    check(without_gil([&] { return call(p, peers.n, n, &fin, &fout, op, sp, st); }), "fcv2_reduce_requant");
     if (!want) return out.result();
     PyObject* pair = PyTuple_New(2);
     if (!pair) throw Raised{};
@@ -298,9 +306,13 @@ PyObject* dispatch_quant(PyObject* const* a) {
     const fcv2_layout_t l = layout(r.H, r.f, FCV2_ROW_ALIGN);
     const int64_t slots = (int64_t)r.T * r.K;
     Given send(a[6]), offsets(a[7]), src(a[8]), ws(a[9]);
-    if (!send) send.made = new_zeros({slots, (int64_t)l.total_bytes}, at::kByte, r.x);
-    if (!offsets) offsets.made = new_zeros({(int64_t)r.E + 1}, at::kInt, r.x);
-    if (!src) src.made = new_tensor({slots}, at::kInt, r.x).fill_(-1);
+    // The kernels define all of send_buf and row_src only when both are ours; one alone is filled the plain way.
+    const bool fresh = !send && !src;
+    if (!send) send.made = new_tensor({slots, (int64_t)l.total_bytes}, at::kByte, r.x);
+    if (!src) src.made = new_tensor({slots}, at::kInt, r.x);
+    if (!send && !fresh) send.made.zero_();
+    if (!src && !fresh) src.made.fill_(-1);
+    if (!offsets) offsets.made = new_tensor({(int64_t)r.E + 1}, at::kInt, r.x);  // every entry is an output of the call
     size_t need = 0;
     check(fcv2_dispatch_workspace_bytes(r.T, r.K, r.E, &need), "fcv2_dispatch_workspace_bytes");
     if (!ws) ws.made = new_tensor({(int64_t)need}, at::kByte, r.x);
@@ -308,8 +320,9 @@ PyObject* dispatch_quant(PyObject* const* a) {
     void *sp = dev(send.get("send_buf"), "send_buf"), *ep = dev(offsets.get("expert_offsets"), "expert_offsets"),
          *rp = dev(src.get("row_src"), "row_src"), *wp = dev(ws.get("workspace"), "workspace"), *st = stream();
     const size_t have = (size_t)ws.get("workspace").numel();
+    const auto call = fresh ? fcv2_dispatch_quant_fresh : fcv2_dispatch_quant;
     check(without_gil([&] {
-              return fcv2_dispatch_quant(xp, (const int32_t*)ip, r.T, r.H, r.K, r.E, &r.f, sp, (int32_t*)ep, (int32_t*)rp, wp, have, st);
+              return call(xp, (const int32_t*)ip, r.T, r.H, r.K, r.E, &r.f, sp, (int32_t*)ep, (int32_t*)rp, wp, have, st);
           }),
           "fcv2_dispatch_quant");
     return three(send, offsets, src);
