@@ -196,25 +196,55 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){a, b}, bf2v));
 }
 
-// ---- encoder core: EPL consecutive bf16 values of this lane -> EPL codes (one per byte) + the group's metadata ----
-// w[d] holds elements 2d (low half) and 2d+1 (high half).  lig = lane index inside the group (LPG = G / EPL lanes).
-// row = this lane's private LDS scratch (at least EPL bytes, 16-byte aligned), free at the time of the call.
-// Spike reserving (Section 3.3): the group's minimum and maximum are set aside (lowest index on ties, the
-// maximum searched among the other positions) and the rest is quantized over [2nd smallest, 2nd largest]:
-// the two smallest composites (key << 16 | position) and the two smallest of (~key << 16 | position) are
-// tracked in one pass; the smallest of each gives a spike and its position, the second the new range.
-template <int BITS, int EPL, int LPG, bool SR>
-__device__ __forceinline__ void quantize_lane(const uint32_t (&w)[EPL / 2], uint32_t lig, uint32_t mode, const float* tabs, uint4* row,
-                                              uint32_t (&c)[EPL / 4], GroupMeta& m) {
-    const uint32_t lbase = lig * (uint32_t)EPL;
-    uint32_t a1, a2, b1, b2;  // two smallest composites (a: minimum side, b: maximum side)
-    const uint32_t key_flip = vreg_const<0x80008000u>();  // in a vector register: the three-register v_bitop3 is the cheap form
+// ---- extremes of a group --------------------------------------------------------------------------------------------------
+// Order-preserving map of fp32 bit patterns to unsigned integers (-0 below +0).
+__device__ __forceinline__ uint32_t key_of_f32(uint32_t x) { return x ^ ((uint32_t)((int32_t)x >> 31) | 0x80000000u); }
+
+#define FCV2_F32_OP3(name, op)                                                                   \
+    __device__ __forceinline__ float name(float a, float b, float c) {                           \
+        float r;                                                                                 \
+        asm(op " %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));                            \
+        return r;                                                                                \
+    }
+#define FCV2_F32_OP2(name, op)                                                                   \
+    __device__ __forceinline__ float name(float a, float b) {                                    \
+        float r;                                                                                 \
+        asm(op " %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));                                        \
+        return r;                                                                                \
+    }
+FCV2_F32_OP3(f_med3, "v_med3_f32")
+FCV2_F32_OP3(f_minimum3, "v_minimum3_f32")  // these two return NaN if any operand is one
+FCV2_F32_OP3(f_maximum3, "v_maximum3_f32")
+FCV2_F32_OP2(f_min, "v_min_f32")
+FCV2_F32_OP2(f_max, "v_max_f32")
+#undef FCV2_F32_OP3
+#undef FCV2_F32_OP2
+__device__ __forceinline__ uint32_t pk_minimum3_f16(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_pk_minimum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ uint32_t pk_maximum3_f16(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Order keys of the two bf16 halves of w: (sign | flip) ^ w, one three-register bitwise operation.
+__device__ __forceinline__ uint32_t keys_of_pair(uint32_t w, uint32_t key_flip) {
+    typedef short short2v __attribute__((ext_vector_type(2)));
+    const uint32_t sign = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2v, w) >> (short2v){15, 15});
+    return __builtin_amdgcn_bitop3_b32(sign, w, key_flip, 0x36);
+}
+
+// Two smallest composites (key << 16 | position) of the lane and two smallest of (~key << 16 | position), for any bit
+// patterns (NaN included).  Positions count inside the lane.
+template <int EPL> __device__ __forceinline__ void lane_extremes_any(const uint32_t (&w)[EPL / 2], uint32_t& a1, uint32_t& a2, uint32_t& b1,
+                                                                     uint32_t& b2) {
+    const uint32_t key_flip = vreg_const<0x80008000u>();
 #pragma unroll
     for (int d = 0; d < EPL / 2; ++d) {
-        typedef short short2v __attribute__((ext_vector_type(2)));
-        const short2v sv = __builtin_bit_cast(short2v, w[d]);
-        const uint32_t sign = __builtin_bit_cast(uint32_t, sv >> (short2v){15, 15});
-        const uint32_t k = __builtin_amdgcn_bitop3_b32(sign, w[d], key_flip, 0x36);  // (sign | flip) ^ w: two order keys
+        const uint32_t k = keys_of_pair(w[d], key_flip);
         uint32_t e0 = (k << 16) | (uint32_t)(2 * d), e1 = (k & 0xFFFF0000u) | (uint32_t)(2 * d + 1);
         FCV2_KEEP(e0);  // keeps each composite one shift-or / and-or instruction (no regrouping with the xor below)
         FCV2_KEEP(e1);
@@ -224,22 +254,141 @@ __device__ __forceinline__ void quantize_lane(const uint32_t (&w)[EPL / 2], uint
             a2 = max(e0, e1);
             b1 = min(f0, f1);
             b2 = max(f0, f1);
-        } else if (SR) {
+        } else {
             push2_pair(a1, a2, e0, e1);
             push2_pair(b1, b2, f0, f1);
-        } else {
-            a1 = min(a1, min(e0, e1));
-            b1 = min(b1, min(f0, f1));
         }
     }
-    a1 += lbase;
-    b1 += lbase;
-    uint32_t klo, khi, imin = 0xFFFFu, imax = 0xFFFFu;
-    if (SR) {
+}
+
+// The two spikes of a group and the two next values (Section 3.3): composites of the minimum (a1), the second smallest (a2), the
+// maximum (b1, b2; key inverted) over the group, positions counted inside the group, lowest index on ties.
+//
+// A bf16 value with a position in the 16 bits below it is an fp32 number, so the two smallest and two largest come out of the
+// fp32 median / minimum / maximum instructions: 8 instructions per pair of elements, where composites of integer order keys
+// (lane_extremes_any) take 12, half of them to build the keys and to invert them for the maximum.  The position stands there
+// inverted, so that of equal values the lowest index wins where the minimum is negative and the maximum is not; the other
+// way round (a group of one sign) the position is looked for again.  NaN or infinite values (an infinity with a position
+// below it is a NaN) make minimum3 / maximum3 return NaN: the wave then takes the integer form.
+template <int EPL, int LPG> __device__ __forceinline__ void group_spikes(const uint32_t (&w)[EPL / 2], uint32_t lbase, uint32_t& a1, uint32_t& a2,
+                                                                         uint32_t& b1, uint32_t& b2) {
+    // Composites as single instructions, opaque to the compiler: it would keep the shifted and masked halves of all elements in
+    // registers from here to the quantizer, which takes the same halves (50 registers more, two waves per SIMD fewer).
+    const uint32_t hi_mask = vreg_const<0xFFFF0000u>();
+    auto pair = [&](int d, bool inverted, float& x, float& y) {
+        const uint32_t p0 = inverted ? (uint32_t)(EPL - 1 - 2 * d) : (uint32_t)(2 * d), p1 = inverted ? p0 - 1u : p0 + 1u;
+        asm("v_lshl_or_b32 %0, %1, 16, %2" : "=v"(x) : "v"(w[d]), "i"(p0));
+        asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(y) : "v"(w[d]), "v"(hi_mask), "i"(p1));
+    };
+    float fa1, fa2, fb1, fb2;
+#pragma unroll
+    for (int d = 0; d < EPL / 2; ++d) {
+        float x, y;
+        pair(d, true, x, y);
+        if (d == 0) {
+            fa1 = f_minimum3(x, y, y);
+            fa2 = f_max(x, y);
+            fb1 = f_maximum3(x, y, y);
+            fb2 = f_min(x, y);
+        } else {
+            const float ta = f_med3(fa1, x, y), tb = f_med3(fb1, x, y);
+            fa1 = f_minimum3(fa1, x, y);
+            fb1 = f_maximum3(fb1, x, y);
+            fa2 = f_min(fa2, ta);
+            fb2 = f_max(fb2, tb);
+        }
+    }
+    constexpr uint32_t kKeep = 0xFFFF0000u | (uint32_t)(EPL - 1);  // value and in-lane position
+    if (!__any(fa1 != fa1 || fb1 != fb1)) {
+        // as integers; the inverted position of a negative number (of a non-negative one on the maximum side) turns back
+        a1 = (key_of_f32(f2u(fa1)) & kKeep) | lbase;
+        a2 = (key_of_f32(f2u(fa2)) & kKeep) | lbase;
+        b1 = (~key_of_f32(f2u(fb1)) & kKeep) | lbase;
+        b2 = (~key_of_f32(f2u(fb2)) & kKeep) | lbase;
+        group_min2<LPG>(a1, a2);
+        group_min2<LPG>(b1, b2);
+        if (__any((int32_t)(a1 | b1) < 0)) {  // a minimum of +0 or above, or a negative maximum
+            float ga1, gb1, gb2;
+#pragma unroll
+            for (int d = 0; d < EPL / 2; ++d) {
+                float x, y;
+                pair(d, false, x, y);
+                if (d == 0) {
+                    ga1 = f_min(x, y);
+                    gb1 = f_max(x, y);
+                    gb2 = f_min(x, y);
+                } else {
+                    const float t = f_med3(gb1, x, y);
+                    ga1 = f_minimum3(ga1, x, y);
+                    gb1 = f_maximum3(gb1, x, y);
+                    gb2 = f_max(gb2, t);
+                }
+            }
+            uint32_t c1 = (key_of_f32(f2u(ga1)) & kKeep) | lbase;
+            uint32_t d1 = (~key_of_f32(f2u(gb1)) & kKeep) | lbase, d2 = (~key_of_f32(f2u(gb2)) & kKeep) | lbase;
+            c1 = group_min<LPG>(c1);
+            group_min2<LPG>(d1, d2);
+            if ((int32_t)a1 < 0) a1 = c1;
+            if ((int32_t)b1 < 0) {
+                b1 = d1;
+                b2 = d2;
+            }
+        }
+    } else {
+        lane_extremes_any<EPL>(w, a1, a2, b1, b2);
+        a1 += lbase;
         a2 += lbase;
+        b1 += lbase;
         b2 += lbase;
         group_min2<LPG>(a1, a2);
         group_min2<LPG>(b1, b2);
+    }
+}
+
+// Smallest and largest order key of a group, no positions.  bf16 bit patterns read as fp16 numbers have the same order (both are
+// sign and magnitude), so the packed three-operand fp16 minimum and maximum take four elements per instruction.  Patterns that
+// are NaN as fp16 (magnitudes from 2^121 up, infinities and NaN) come through as NaN: the wave then compares integer keys.
+template <int EPL, int LPG> __device__ __forceinline__ void group_range(const uint32_t (&w)[EPL / 2], uint32_t& klo, uint32_t& khi) {
+    const uint32_t key_flip = vreg_const<0x80008000u>();
+    uint32_t mn = w[0], mx = w[0], a, b;
+#pragma unroll
+    for (int d = 0; d < EPL / 2; d += 2) {
+        mn = pk_minimum3_f16(mn, w[d], w[d + 1]);
+        mx = pk_maximum3_f16(mx, w[d], w[d + 1]);
+    }
+    const uint32_t top = max(max((mn & 0x7FFFu), (mn >> 16) & 0x7FFFu), max((mx & 0x7FFFu), (mx >> 16) & 0x7FFFu));
+    if (!__any(top > 0x7C00u)) {
+        const uint32_t kn = keys_of_pair(mn, key_flip), kx = ~keys_of_pair(mx, key_flip);
+        a = min(kn << 16, kn & 0xFFFF0000u);
+        b = min(kx << 16, kx & 0xFFFF0000u);
+    } else {
+        a = b = 0xFFFFFFFFu;
+#pragma unroll
+        for (int d = 0; d < EPL / 2; ++d) {
+            const uint32_t k = keys_of_pair(w[d], key_flip), n = ~k;
+            a = umin3(a, k << 16, k & 0xFFFF0000u);
+            b = umin3(b, n << 16, n & 0xFFFF0000u);
+        }
+    }
+    a = group_min<LPG>(a);
+    b = group_min<LPG>(b);
+    klo = a >> 16;
+    khi = (~b) >> 16;
+}
+
+// ---- encoder core: EPL consecutive bf16 values of this lane -> EPL codes (one per byte) + the group's metadata ----
+// w[d] holds elements 2d (low half) and 2d+1 (high half).  lig = lane index inside the group (LPG = G / EPL lanes).
+// row = this lane's private LDS scratch (at least EPL bytes, 16-byte aligned), free at the time of the call.
+// Spike reserving (Section 3.3): the group's minimum and maximum are set aside (lowest index on ties, the
+// maximum searched among the other positions) and the rest is quantized over [2nd smallest, 2nd largest].
+template <int BITS, int EPL, int LPG, bool SR>
+__device__ __forceinline__ void quantize_lane(const uint32_t (&w)[EPL / 2], uint32_t lig, uint32_t mode, const float* tabs, uint4* row,
+                                              uint32_t (&c)[EPL / 4], GroupMeta& m) {
+    const uint32_t lbase = lig * (uint32_t)EPL;
+    uint32_t klo, khi, imin = 0xFFFFu, imax = 0xFFFFu;
+    if (SR) {
+        uint32_t a1, a2, b1, b2;
+        group_spikes<EPL, LPG>(w, lbase, a1, a2, b1, b2);
         imin = a1 & 0xFFFFu;
         // a constant group: the first maximum is the minimum itself, take the next position
         imax = ((b1 & 0xFFFFu) == imin) ? (b2 & 0xFFFFu) : (b1 & 0xFFFFu);
@@ -248,10 +397,7 @@ __device__ __forceinline__ void quantize_lane(const uint32_t (&w)[EPL / 2], uint
         m.sv = bf16_of_key(a1 >> 16) | (bf16_of_key((~b1) >> 16) << 16);
         m.si = imin | (imax << 8);
     } else {
-        a1 = group_min<LPG>(a1);
-        b1 = group_min<LPG>(b1);
-        klo = a1 >> 16;
-        khi = (~b1) >> 16;
+        group_range<EPL, LPG>(w, klo, khi);
         m.sv = 0;
         m.si = 0;
     }
