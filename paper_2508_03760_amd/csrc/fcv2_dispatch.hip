@@ -6,7 +6,8 @@
 namespace fcv2 {
 
 // ---- dispatch: stable counting sort of the routed copies by expert, then quantize-and-scatter ------------------------
-// Three launches, no order-dependent atomics, no waiting between blocks:
+// No order-dependent atomics, no waiting between blocks.  Small routings are one launch, the quantize-and-scatter kernel
+// planning for itself (self_planned, plan_block); otherwise three:
 //   1. k_dispatch_count_rank   per chunk of 256 routed slots: the chunk's histogram over the experts, and for every slot
 //                              its stable rank among the chunk's slots of the same expert (one byte);
 //   2. k_dispatch_scan_chunks  per expert: exclusive prefix of the histograms over the chunks (in place) and the total;
@@ -287,14 +288,101 @@ constexpr int kRowsBlockMax = 512;  // threads of the row-staged kernel (8 waves
 // Dynamic LDS: per wave the transpose scratch | the records | the destination rows | the tables.
 struct DispatchPlan {  // what the planning launches left in the workspace, and the two index outputs of the call
     const int32_t* ids;
-    const int32_t* hist;
+    const int32_t* hist;  // null: no planning launches ran, every block plans for itself (self_planned)
     const int32_t* totals;
     const uint8_t* lrank;
     int32_t* expert_offsets;
     int32_t* row_src;
     uint32_t E;
+    uint32_t totals_last;  // last entry of totals that may be read
     uint32_t fresh_rows;  // T * K when send buffer and row_src hold no values yet (fcv2_fresh.h), else 0
 };
+
+// The whole plan of a small routing, made by every block for itself under its token loads instead of by two launches before
+// the kernel.  Every block counts all routed slots in LDS, per expert the total in the low and the slots before the block's
+// own in the high half of one word (integer additions: their order does not matter), wave 0 turns them into
+// start[e] = first row of the expert + the slots of it in front of this block, start[E] = all routed copies.  Returns the
+// rank of thread i < 64's slot among the block's slots of the same expert; block 0 writes expert_offsets.
+__device__ __forceinline__ uint32_t plan_block(const DispatchPlan& plan, uint32_t n_slots, uint32_t first, uint32_t n_slots_here, int32_t my_e,
+                                               uint32_t* counts, uint32_t* start) {
+    constexpr uint32_t BATCH = 8;  // loads of four ids a thread has in flight: 8192 slots are one round of 256 threads
+    // Neighbouring lanes often meet at a popular expert: up to 16 copies of the counters, a lane uses copy lane % copies.
+    // Copies lie an odd number of words apart, so that the copies of one counter sit in different banks.
+    const uint32_t stride = plan.E | 1u, room = min(blockDim.x >> 6, 2u) * (kWaveScratchBytes / 4);
+    uint32_t copies = 1;
+    if (n_slots > 4 * blockDim.x)
+        while (copies < 16 && 2 * copies * stride <= room) copies *= 2;
+    uint32_t* mine = counts + (threadIdx.x & (copies - 1)) * stride;
+    for (uint32_t i = threadIdx.x; i < copies * stride; i += blockDim.x) counts[i] = 0u;
+    __syncthreads();
+    const int4* ids4 = reinterpret_cast<const int4*>(plan.ids);
+    const uint32_t n4 = n_slots >> 2;
+    auto count = [&](int32_t e, uint32_t i) {
+        if ((uint32_t)e < plan.E) atomicAdd(&mine[e], i < first ? 0x10001u : 1u);
+    };
+    for (uint32_t i0 = threadIdx.x; i0 < n4; i0 += BATCH * blockDim.x) {
+        int4 e[BATCH];
+#pragma unroll
+        for (uint32_t k = 0; k < BATCH; ++k) e[k] = ids4[min(i0 + k * blockDim.x, n4 - 1u)];
+#pragma unroll
+        for (uint32_t k = 0; k < BATCH; ++k) {
+            const uint32_t i = i0 + k * blockDim.x;
+            if (i >= n4) break;
+            count(e[k].x, 4 * i);
+            count(e[k].y, 4 * i + 1);
+            count(e[k].z, 4 * i + 2);
+            count(e[k].w, 4 * i + 3);
+        }
+    }
+    const uint32_t rest = 4 * n4 + threadIdx.x;
+    if (rest < n_slots) count(plan.ids[rest], rest);
+    __syncthreads();
+    if (copies > 1) {
+        for (uint32_t e = threadIdx.x; e < plan.E; e += blockDim.x) {
+            uint32_t both = 0;
+            for (uint32_t c = 0; c < copies; c += 2) both += counts[c * stride + e] + counts[(c + 1) * stride + e];
+            counts[e] = both;
+        }
+        __syncthreads();
+    }
+    uint32_t rank = 0;
+    if (threadIdx.x < 64) {
+        const uint32_t lane = threadIdx.x;
+        const uint32_t per = (plan.E + 63) / 64, e0 = min(lane * per, plan.E), e1 = min(e0 + per, plan.E);  // at most 4 each
+        uint32_t both[4], sum = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) both[k] = counts[min(e0 + k, plan.E - 1u)];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            if (e0 + k >= e1) both[k] = 0;
+            sum += both[k] & 0xFFFFu;
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t up = __shfl_up(inc, d);
+            if ((int)lane >= d) inc += up;
+        }
+        uint32_t run = inc - sum;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            if (e0 + k < e1) {
+                start[e0 + k] = run + (both[k] >> 16);
+                if (blockIdx.x == 0) plan.expert_offsets[e0 + k] = (int32_t)run;
+            }
+            run += both[k] & 0xFFFFu;
+        }
+        if (lane == 63) {
+            start[plan.E] = inc;
+            if (blockIdx.x == 0) plan.expert_offsets[plan.E] = (int32_t)inc;
+        }
+        for (uint32_t j = 0; j < n_slots_here; ++j) {
+            const int32_t ej = __builtin_amdgcn_readlane(my_e, (int)j);
+            rank += (ej == my_e && j < lane) ? 1u : 0u;
+        }
+    }
+    return rank;
+}
 
 template <int BITS, int LPG, bool SR, bool INT_META>
 __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* __restrict__ x, uint32_t T, uint32_t lanes_per_row,
@@ -329,7 +417,8 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
     const uint32_t e0 = min(lane * per, plan.E), e1 = min(e0 + per, plan.E);
     int32_t tot[4];  // up to 256 experts: the lane's totals, four independent loads
 #pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) tot[k] = plan.totals[min(e0 + k, plan.E - 1u)];
+    for (uint32_t k = 0; k < 4; ++k) tot[k] = plan.totals[min(e0 + k, plan.totals_last)];
+    const bool self = plan.hist == nullptr;
     const bool has_tile = wave * 64 < block_lanes;  // whole waves past the block's last row only help with the copies
     TileIn in = {};
     if (has_tile) in = tile_load(x, (row0 * lanes_per_row + wave * 64) * 4, lane, (block_lanes - wave * 64) * 4);
@@ -338,7 +427,11 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
     for (uint32_t k = 0; k < 4; ++k)
         if (per > 4 || e0 + k >= e1) tot[k] = 0;
     if (my_e < 0 || (uint32_t)my_e >= plan.E) my_e = -1;
-    if (wave == 0) {
+    int32_t my_before = 0, my_rank = 0;
+    if (self) {
+        my_rank = (int32_t)plan_block(plan, T * K, row0 * K, n_slots_here, my_e, reinterpret_cast<uint32_t*>(smem),
+                                      reinterpret_cast<uint32_t*>(start));
+    } else if (wave == 0) {
         int32_t my_sum = tot[0] + tot[1] + tot[2] + tot[3];
         if (per > 4)  // more than 256 experts: read in a loop (each read waited for; such routings are rare)
             for (uint32_t e = e0; e < e1; ++e) my_sum += plan.totals[e];
@@ -374,8 +467,7 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
         for (uint32_t t = threadIdx.x; t < (uint32_t)kScaleTables; t += blockDim.x) tabs[t] = kScaleTablesInit.v[t];
     }
     __syncthreads();
-    int32_t my_before = 0, my_rank = 0;
-    if (my_e >= 0) {
+    if (!self && my_e >= 0) {
         my_before = plan.hist[(uint64_t)(my_slot / kChunk) * plan.E + my_e];
         my_rank = (int32_t)plan.lrank[my_slot];
     }
@@ -512,6 +604,18 @@ template <int BITS, int G, bool SR> struct LaunchDispatch {
     }
 };
 
+// Whether every block of the row-staged kernel plans for itself (plan_block) instead of reading what two launches before it
+// prepared.  A block then counts all routed slots, so the work grows with slots x blocks, while the two launches cost 2 to
+// 4 us whatever the size.  Measured on the MI355X (4 bits, us per call, planned by launches -> by itself): 64 tokens x 8 on
+// 256 experts 11.0 -> 7.4; 1021 x 6 on 64 (2 M) 12.2 -> 10.1; 1024 x 8 on 256 (8 M) 15.2 -> 13.3; 2048 x 2 on 8 (8 M)
+// 12.9 -> 11.8; from 16 M the launches win: 2048 x 4 on 64 15.0 -> 15.5, 4096 x 2 of 1024 elements 11.0 -> 13.1.
+// The block's own slots are ranked by one wave, the expert counts are four to a lane and the ids are read 16 bytes at a time.
+static bool self_planned(const RowsPlan& rp, const int32_t* ids, uint32_t T, uint32_t K, uint32_t E) {
+    if (rp.rows == 0 || rp.rows * K > 64u || E > 256u || (reinterpret_cast<uintptr_t>(ids) & 15u) != 0) return false;
+    const uint64_t n_slots = (uint64_t)T * K, blocks = (T + rp.rows - 1) / rp.rows;
+    return n_slots <= 8192u && n_slots * blocks <= (1u << 23);
+}
+
 int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E,
                     uint8_t* send, int32_t* expert_offsets, int32_t* row_src, void* ws, const Rec& rec, uint32_t row_bytes,
                     bool fresh, hipStream_t st) {
@@ -520,13 +624,18 @@ int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, ui
     int32_t* totals = (int32_t*)((uint8_t*)ws + w.off_totals);
     uint8_t* lrank = (uint8_t*)ws + w.off_lrank;
     int32_t* dest = (int32_t*)((uint8_t*)ws + w.off_dest);
+    const RowsPlan rp = rows_plan(H / kEplStream, K, row_bytes, meta_mode_of(fmt) == kMetaInt, E);
+    if (self_planned(rp, ids, T, K, E)) {
+        const DispatchPlan plan = {ids, nullptr, ids, nullptr, expert_offsets, row_src, E, 0u, fresh ? w.n_slots : 0u};
+        return by_format<LaunchDispatch>(fmt, x, T, H, K, plan, dest, send, rec, row_bytes, meta_mode_of(fmt), st);
+    }
     const size_t mask_bytes = (size_t)(kChunk / 64) * E * 8;  // lane masks per wave and expert: 8 KiB at 256 experts
     const int rc = mask_bytes <= 32 * 1024
                        ? launch(k_dispatch_count_rank<true>, dim3(w.n_chunks), dim3(kChunk), mask_bytes, st, ids, w.n_slots, E, hist, lrank)
                        : launch(k_dispatch_count_rank<false>, dim3(w.n_chunks), dim3(kChunk), mask_bytes / 2, st, ids, w.n_slots, E, hist, lrank);
     if (rc != FCV2_OK) return FCV2_ERR_LAUNCH;
     if (launch(k_dispatch_scan_chunks, dim3(E), dim3(64), 0, st, hist, w.n_chunks, E, totals) != FCV2_OK) return FCV2_ERR_LAUNCH;
-    const DispatchPlan plan = {ids, hist, totals, lrank, expert_offsets, row_src, E, fresh ? w.n_slots : 0u};
+    const DispatchPlan plan = {ids, hist, totals, lrank, expert_offsets, row_src, E, E - 1u, fresh ? w.n_slots : 0u};
     return by_format<LaunchDispatch>(fmt, x, T, H, K, plan, dest, send, rec, row_bytes, meta_mode_of(fmt), st);
 }
 

@@ -1,0 +1,47 @@
+"""Small routings, which the quantize-and-scatter kernel plans by itself, at the edges of that rule: against the oracle, and
+against the same call planned by its own launches (which ids that are not 16-byte aligned take)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2508_03760_amd import fcv2
+from paper_2508_03760_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SR, INT = fcv2.F_SPIKE, fcv2.F_META_INT
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("T,H,K,E", [
+    (1, 128, 1, 1), (1, 384, 3, 3),      # fewer than four slots
+    (5, 2048, 3, 7), (67, 1024, 5, 33),      # slots no multiple of four, blocks of one wave
+    (61, 7168, 8, 255), (64, 7168, 8, 256),  # the most experts
+    (64, 7168, 8, 257),                      # one more: planned by launches
+    (1023, 1024, 8, 64), (1025, 1024, 8, 64),  # the most slots (8,192) lie between these
+    (300, 256, 4, 16), (300, 128, 4, 16),    # 8 rows a block; 16 rows of 4 slots, the most a wave ranks
+    (1500, 2560, 2, 8),                      # many slots of few experts
+    (257, 16384, 8, 2),                      # eight waves a block
+])
+@pytest.mark.parametrize("fmt", [(4, 32, SR), (2, 128, SR | INT)])
+def test_both_plans_match_the_oracle(T, H, K, E, fmt):
+    x = W.tensor(3, 1, rows=T, cols=H)
+    rng = np.random.default_rng(T * 1009 + E)
+    ids = np.minimum(rng.geometric(3.0 / (E + 2), size=(T, K)) - 1, E - 1).astype(np.int32)  # popular experts, repeats allowed
+    ids[rng.random(ids.shape) < 0.1] = -1
+    xd = torch.from_numpy(np.ascontiguousarray(x).view(np.int16)).to(DEV).view(torch.bfloat16).view(T, H)
+    room = torch.empty(T * K + 4, dtype=torch.int32, device=DEV)
+    got = []
+    for off in (0, 1):
+        d = room[off:off + T * K].view(T, K)
+        d.copy_(torch.from_numpy(ids))
+        assert d.data_ptr() % 16 == 4 * off
+        got.append(fcv2.dispatch_quant(xd, d, E, *fmt))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    send_o, offs_o, src_o = O.dispatch_quant(x.reshape(T, H), ids, E, *fmt)
+    R = int(offs_o[-1])
+    send, offs, src = (t.cpu().numpy() for t in got[0])
+    assert np.array_equal(offs, offs_o) and np.array_equal(src[:R], src_o[:R])
+    assert np.array_equal(send.reshape(T * K, -1)[:R], np.asarray(send_o).reshape(-1, send.shape[-1])[:R])
