@@ -365,7 +365,7 @@ template <int BITS> FCV2_HD void codes_pairs(uint32_t p8lo, uint32_t p8hi, uint3
 #undef FCV2_SHIFTED
 }
 
-// ---- 16 elements of a lane -> 8 registers of (element | element) 16-bit halves, for 2, 3 and 4 bits --------------
+// ---- 16 elements of a lane -> 8 registers of (element | element) 16-bit halves, for 2 to 7 bits ------------------
 // As above, but the fields are only masked, never moved to bit 0: each half ends up holding code << pos with
 // zeros around it, and the consumer folds 2^-pos into the scale it multiplies the half with (a half read as an
 // fp16 denormal is an exact integer multiple of 2^-24 at any position below bit 10).  PairMap says which element
@@ -395,6 +395,18 @@ template <> struct PairMap<4> {  // nibbles at offset 0 and 4 of each half, dire
     static constexpr int k_of(int e) { return (e & 3) + 4 * (e >> 3); }
     static constexpr bool in_hi(int e) { return ((e >> 2) & 1) != 0; }
 };
+// 5, 6 and 7 bits: register k holds elements k and k + 8.  Element k of a half sits at bit 2k of the 2-bit plane word, at
+// bit k of the 1-bit plane's half and at nibble k & 3 of a register that holds four nibbles per half; the plane shifts
+// in codes_pairs16_wide bring its fields next to each other at `pos`.
+struct PairMapWide {
+    static constexpr int lo(int k) { return k; }
+    static constexpr int hi(int k) { return k + 8; }
+    static constexpr int k_of(int e) { return e & 7; }
+    static constexpr bool in_hi(int e) { return e >= 8; }
+};
+template <> struct PairMap<5> : PairMapWide { static constexpr int pos(int k) { return k & 1; } };
+template <> struct PairMap<6> : PairMapWide { static constexpr int pos(int k) { return k < 3 ? 2 * k : k < 6 ? 2 * (k - 3) : 2 * (k - 6); } };
+template <> struct PairMap<7> : PairMapWide { static constexpr int pos(int k) { return k & 1; } };
 
 template <int BITS> constexpr bool pair_map_consistent() {
     using M = PairMap<BITS>;
@@ -402,7 +414,9 @@ template <int BITS> constexpr bool pair_map_consistent() {
         if (M::k_of(M::lo(k)) != k || M::in_hi(M::lo(k)) || M::k_of(M::hi(k)) != k || !M::in_hi(M::hi(k)) || M::pos(k) + BITS > 10) return false;
     return true;
 }
-static_assert(pair_map_consistent<2>() && pair_map_consistent<3>() && pair_map_consistent<4>(), "PairMap: element <-> (register, half) maps disagree");
+static_assert(pair_map_consistent<2>() && pair_map_consistent<3>() && pair_map_consistent<4>() && pair_map_consistent<5>() &&
+                  pair_map_consistent<6>() && pair_map_consistent<7>(),
+              "PairMap: element <-> (register, half) maps disagree");
 
 // Every mask below is a literal of a two-operand `and` (see the note on instruction forms at the top), shifts go to
 // the right wherever a plain shift does, and the one wrap-around that is needed (element 0 of the 3-bit layout) is a
@@ -434,6 +448,56 @@ FCV2_HD void codes_pairs16_b3(uint32_t p2, uint32_t S, uint32_t (&Q)[8]) {
     Q[7] = and_lit<0x03800380u>(We8);  // elements 8, 0
 }
 
+// 5, 6 and 7 bits.  The nibbles of elements k and k + 8 meet in one register (a byte permute each for k < 4 and k >= 4); then
+// one shift per plane and register puts a nibble directly above its lower bits, a bit-select joins them and a literal mask
+// keeps the element: 5.6, 5.3 and 8.3 VALU cycles per element by the costs above, against 6.9, 6.9 and 11.4 for codes_pairs,
+// which moves every field to bit 0 and joins the planes with and-or instructions that read scalar masks.
+// reduce_requant of 16 M elements, 8 peers, groups of 128 / 256, us before -> after: 5 bits 31.8 -> 31.1 / 31.4 -> 30.7, 6 bits
+// 32.3 -> 32.1 / 32.7 -> 31.8, 7 bits 37.6 -> 35.8 / 37.0 -> 34.9.
+template <int BITS> FCV2_HD void codes_pairs16_wide(uint32_t p4a, uint32_t p4b, uint32_t p2, uint32_t p1, uint32_t (&Q)[8]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint32_t na = __builtin_amdgcn_perm(p4b, p4a, 0x05040100u), nb = __builtin_amdgcn_perm(p4b, p4a, 0x07060302u);
+#else
+    const uint32_t na = (p4a & 0xFFFFu) | (p4b << 16), nb = (p4a >> 16) | (p4b & 0xFFFF0000u);
+#endif
+    const uint32_t x1 = (p1 << 8) | p1;  // bit k of each half: elements k and k + 8 (further bits above them)
+    if (BITS == 5) {
+        const uint32_t n0 = vreg_const<0x001E001Eu>(), n1 = vreg_const<0x003C003Cu>();
+        const uint32_t x12 = x1 >> 2, x14 = x1 >> 4, x16 = x1 >> 6;
+        Q[0] = and_lit<0x001F001Fu>(bit_select(n0, na << 1, x1));
+        Q[1] = and_lit<0x003E003Eu>(bit_select(n1, na >> 2, x1));
+        Q[2] = and_lit<0x001F001Fu>(bit_select(n0, na >> 7, x12));
+        Q[3] = and_lit<0x003E003Eu>(bit_select(n1, na >> 10, x12));
+        Q[4] = and_lit<0x001F001Fu>(bit_select(n0, nb << 1, x14));
+        Q[5] = and_lit<0x003E003Eu>(bit_select(n1, nb >> 2, x14));
+        Q[6] = and_lit<0x001F001Fu>(bit_select(n0, nb >> 7, x16));
+        Q[7] = and_lit<0x003E003Eu>(bit_select(n1, nb >> 10, x16));
+    } else if (BITS == 6) {
+        const uint32_t n0 = vreg_const<0x003C003Cu>(), n2 = vreg_const<0x00F000F0u>(), n4 = vreg_const<0x03C003C0u>();
+        const uint32_t x26 = p2 >> 6, x2c = p2 >> 12;
+        Q[0] = and_lit<0x003F003Fu>(bit_select(n0, na << 2, p2));
+        Q[1] = and_lit<0x00FC00FCu>(bit_select(n2, na, p2));
+        Q[2] = and_lit<0x03F003F0u>(bit_select(n4, na >> 2, p2));
+        Q[3] = and_lit<0x003F003Fu>(bit_select(n0, na >> 10, x26));
+        Q[4] = and_lit<0x00FC00FCu>(bit_select(n2, nb << 4, x26));
+        Q[5] = and_lit<0x03F003F0u>(bit_select(n4, nb << 2, x26));
+        Q[6] = and_lit<0x003F003Fu>(bit_select(n0, nb >> 6, x2c));
+        Q[7] = and_lit<0x00FC00FCu>(bit_select(n2, nb >> 8, x2c));
+    } else {
+        const uint32_t n0 = vreg_const<0x00780078u>(), n1 = vreg_const<0x00F000F0u>();   // the nibble ...
+        const uint32_t e0 = vreg_const<0x00010001u>(), e1 = vreg_const<0x00020002u>();   // ... and the extra bit, at pos 0 and 1
+        const uint32_t x12 = x1 >> 2, x14 = x1 >> 4, x16 = x1 >> 6;
+        Q[0] = and_lit<0x007F007Fu>(bit_select(e0, x1, bit_select(n0, na << 3, p2 << 1)));
+        Q[1] = and_lit<0x00FE00FEu>(bit_select(e1, x1, bit_select(n1, na, p2)));
+        Q[2] = and_lit<0x007F007Fu>(bit_select(e0, x12, bit_select(n0, na >> 5, p2 >> 3)));
+        Q[3] = and_lit<0x00FE00FEu>(bit_select(e1, x12, bit_select(n1, na >> 8, p2 >> 4)));
+        Q[4] = and_lit<0x007F007Fu>(bit_select(e0, x14, bit_select(n0, nb << 3, p2 >> 7)));
+        Q[5] = and_lit<0x00FE00FEu>(bit_select(e1, x14, bit_select(n1, nb, p2 >> 8)));
+        Q[6] = and_lit<0x007F007Fu>(bit_select(e0, x16, bit_select(n0, nb >> 5, p2 >> 11)));
+        Q[7] = and_lit<0x00FE00FEu>(bit_select(e1, x16, bit_select(n1, nb >> 8, p2 >> 12)));
+    }
+}
+
 template <int BITS> FCV2_HD void codes_pairs16(uint32_t p4a, uint32_t p4b, uint32_t p2, uint32_t p1, uint32_t (&Q)[8]) {
     if (BITS == 2) {
         const uint32_t B = p2 >> 10;  // element 5 at bit 0, element 13 at bit 16
@@ -447,6 +511,8 @@ template <int BITS> FCV2_HD void codes_pairs16(uint32_t p4a, uint32_t p4b, uint3
         Q[7] = and_lit<0x00300030u>(B);
     } else if (BITS == 3) {
         codes_pairs16_b3(p2, spread_extra_bits16(p1), Q);
+    } else if (BITS > 4) {
+        codes_pairs16_wide<BITS>(p4a, p4b, p2, p1, Q);
     } else {
         const uint32_t Ba = p4a >> 8, Bb = p4b >> 8;
         Q[0] = and_lit<0x000F000Fu>(p4a);

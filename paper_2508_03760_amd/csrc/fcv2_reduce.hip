@@ -55,15 +55,36 @@ template <int BITS> struct UnitPairMap {  // codes_pairs on two units of 8: unit
     static constexpr int pos(int) { return 0; }
 };
 
+template <int BITS> struct PairCodes {
+    static constexpr bool kInPlace = BITS <= 7;  // the fields are only masked, never moved to bit 0 (codes_pairs16)
+    using Map = typename std::conditional<kInPlace, PairMap<(kInPlace ? BITS : 2)>, UnitPairMap<BITS>>::type;
+};
+
+// The codes of half h (16 elements) of a lane's planes as pair registers.
+template <int BITS, int EPL> __device__ __forceinline__ void pair_codes(const RawPlanes<EPL>& r, int h, uint32_t (&Q)[8]) {
+    using P = Planes<BITS>;
+    if constexpr (PairCodes<BITS>::kInPlace) {
+        const uint32_t p1 = P::w1 ? (EPL == 16 ? r.p1 : (h == 0 ? and_lit<0xFFFFu>(r.p1) : r.p1 >> 16)) : 0u;
+        codes_pairs16<BITS>(P::w4 ? r.p4[(2 * h) % (EPL / 8)] : 0u, P::w4 ? r.p4[(2 * h + 1) % (EPL / 8)] : 0u,
+                            P::w2 ? r.p2[h % ((EPL + 15) / 16)] : 0u, p1, Q);
+    } else {
+#pragma unroll
+        for (int uu = 0; uu < 2; ++uu) {
+            uint32_t Q4[4];
+            codes_pairs<BITS>(r.p8[2 * (2 * h + uu)], r.p8[2 * (2 * h + uu) + 1], 0u, 0u, 0u, Q4);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) Q[4 * uu + k] = Q4[k];
+        }
+    }
+}
+
 // (Measured and not used: taking the spread of the 3-bit format's extra bits from two 256-entry LDS tables instead of
 // computing it -- 12 VALU cycles instead of 35 per peer and 16 elements -- made the kernel 7 % slower: two more LDS
 // reads at scattered addresses per peer, in front of everything else the peer needs.)
 template <int BITS, int EPL, bool SR, int PATCH>
 __device__ __forceinline__ void add_peer_values(const RawPlanes<EPL>& r, const GroupMeta& m, uint32_t lig, uint4* row, float (&acc)[EPL]) {
     typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-    using P = Planes<BITS>;
-    constexpr bool IN_PLACE = BITS <= 4;  // narrow codes are only masked where they stand (codes_pairs16)
-    using M = typename std::conditional<IN_PLACE, PairMap<(IN_PLACE ? BITS : 2)>, UnitPairMap<BITS>>::type;
+    using M = typename PairCodes<BITS>::Map;
     const float s = m.s, lo = m.lo;
     uint32_t relmin = 0xFFFFFFFFu, relmax = 0xFFFFFFFFu, t = 0u;
     if (SR) {
@@ -85,23 +106,7 @@ __device__ __forceinline__ void add_peer_values(const RawPlanes<EPL>& r, const G
     };
     auto codes16 = [&](auto fast_tag, int h, Codes16& c) {
         if constexpr (decltype(fast_tag)::value) {
-            if constexpr (IN_PLACE) {
-                const uint32_t p1 = P::w1 ? (EPL == 16 ? r.p1 : (h == 0 ? and_lit<0xFFFFu>(r.p1) : r.p1 >> 16)) : 0u;
-                codes_pairs16<BITS>(P::w4 ? r.p4[(2 * h) % (EPL / 8)] : 0u, P::w4 ? r.p4[(2 * h + 1) % (EPL / 8)] : 0u,
-                                    P::w2 ? r.p2[h % ((EPL + 15) / 16)] : 0u, p1, c.Q);
-            } else {
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu) {
-                    const int u = 2 * h + uu;
-                    uint32_t Q4[4];
-                    const uint32_t p4 = P::w4 ? r.p4[u] : 0u;
-                    const uint32_t p2 = P::w2 ? ((r.p2[u >> 1] >> (16 * (u & 1))) & 0xFFFFu) : 0u;
-                    const uint32_t p1 = P::w1 ? ((r.p1 >> (8 * u)) & 0xFFu) : 0u;
-                    codes_pairs<BITS>(P::w8 ? r.p8[2 * u] : 0u, P::w8 ? r.p8[2 * u + 1] : 0u, p4, p2, p1, Q4);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) c.Q[4 * uu + k] = Q4[k];
-                }
-            }
+            pair_codes<BITS, EPL>(r, h, c.Q);
         } else {
 #pragma unroll
             for (int uu = 0; uu < 2; ++uu) {

@@ -101,6 +101,9 @@ int hc_pairs16_of_planes(int bits, uint32_t p4a, uint32_t p4b, uint32_t p2, uint
         case 2: return pairs16_of_planes<2>(p4a, p4b, p2, p1, codes);
         case 3: return pairs16_of_planes<3>(p4a, p4b, p2, p1, codes);
         case 4: return pairs16_of_planes<4>(p4a, p4b, p2, p1, codes);
+        case 5: return pairs16_of_planes<5>(p4a, p4b, p2, p1, codes);
+        case 6: return pairs16_of_planes<6>(p4a, p4b, p2, p1, codes);
+        case 7: return pairs16_of_planes<7>(p4a, p4b, p2, p1, codes);
     }
     return -1;
 }

@@ -159,7 +159,7 @@ def test_plane_packing_sequences_match_oracle(hc, bits):
         assert np.array_equal(back, codes), (bits, codes, back)
 
 
-@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("bits", [2, 3, 4, 5, 6, 7])
 def test_sixteen_element_pair_decoding(hc, bits):
     """The reduce kernel's decoder for 16 elements per lane: planes packed by the oracle come back as the same codes,
     every 16-bit half holds code << pos and nothing else."""
