@@ -270,6 +270,119 @@ void k_reduce_requant(PeerPtrs peers, int n_peers, uint32_t n_lanes, Rec rec_in,
     if (lig == 0) store_meta<SR>(out, rec_out, L / LPG, m, meta_mode_out);
 }
 
+// Small payloads, 2 to 8 peers.  With 16 elements and all peers per lane a payload of half a million elements is less than one
+// wave per SIMD, on half of the compute units, and what the call takes is one wave's chain through its peers: 0.3 us for each
+// (unpacking, the overlay's trip through LDS, the wait for the next loads).  Here the peers of a tile of 1024 elements go to different waves of a block: wave w decodes peer w into LDS (the spikes simply
+// overwrite their slots there), then two waves add the values up in peer order, 8 elements a lane, and quantize.
+// Values of 4 consecutive elements are one 16-byte piece; a lane's four pieces are turned by its number, so that the writes of
+// eight neighbouring lanes (64 bytes apart) fall into different bank groups.
+constexpr uint32_t kSmallTile = 1024, kSmallPeers = 8;
+__device__ __forceinline__ uint32_t small_piece(uint32_t lane, uint32_t q) { return lane * 4 + ((q + (lane >> 1)) & 3u); }
+
+template <int BITS, int G, bool SR, bool INT_META>
+__global__ __launch_bounds__(64 * kSmallPeers) void k_reduce_small(PeerPtrs peers, int n_peers, uint32_t n, Rec rec_in, uint8_t* __restrict__ out,
+                                                                   Rec rec_out, float* __restrict__ sum_out, uint32_t meta_mode_in,
+                                                                   uint32_t meta_mode_out_arg) {
+    const uint32_t meta_mode_out = meta_mode_out_arg & 3u;
+    extern __shared__ uint4 vals[];                     // [n_peers][kSmallTile / 4]
+    __shared__ float tabs[INT_META ? kScaleTables : 1];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t tile0 = blockIdx.x * kSmallTile;
+    if (INT_META) {
+        for (uint32_t t = threadIdx.x; t < (uint32_t)kScaleTables; t += blockDim.x) tabs[t] = kScaleTablesInit.v[t];
+        __syncthreads();
+    }
+    const uint32_t L = tile0 / 16 + lane;
+    if (L < n / 16) {
+        constexpr int EPL = 16, LPG = G / EPL;
+        using Codes = PairCodes<BITS>;
+        using M = typename Codes::Map;
+        typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+        const BufferSrc src = buffer_src(peers.base[wave], rec_in.total);
+        const MetaOffsets mo = meta_offsets<LPG, SR>(rec_in, L, meta_mode_in);
+        const RawPlanes<EPL> r = load_planes<BITS, EPL>(src, rec_in, L);
+        const uint32_t mraw = ld32(src, mo.at), mraw2 = (LPG < 4 && SR) ? ld32(src, mo.at2) : 0u;
+        const GroupMeta m = (INT_META && meta_mode_in == kMetaInt) ? spread_meta<LPG, SR, true>(mraw, mraw2, mo, tabs, rec_in.idx_bf16)
+                                                                   : spread_meta<LPG, SR, false>(mraw, mraw2, mo, tabs, rec_in.idx_bf16);
+        float v[16];
+        if (m.s < 0x1p+100f) {  // codes as fp16 denormals, as in add_peer_values
+            uint32_t Q[8];
+            pair_codes<BITS, EPL>(r, 0, Q);
+            float mult[9];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) mult[q] = m.s * __builtin_ldexpf(1.0f, 24 - q);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const half2v hh = __builtin_bit_cast(half2v, Q[M::k_of(e)]);
+                v[e] = __builtin_fmaf(M::in_hi(e) ? (float)hh.y : (float)hh.x, mult[M::pos(M::k_of(e))], m.lo);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float q8[8];
+                unit_codes<BITS, EPL>(r, u, q8);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[8 * u + j] = __fmaf_rn(q8[j], m.s, m.lo);
+            }
+        }
+        uint4* mine = vals + wave * (kSmallTile / 4);
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+            mine[small_piece(lane, q)] = make_uint4(f2u(v[4 * q]), f2u(v[4 * q + 1]), f2u(v[4 * q + 2]), f2u(v[4 * q + 3]));
+        if (SR) {
+            const uint32_t lig = lane & (LPG - 1);
+            const uint32_t rmin = (m.si & 0xFFu) - lig * 16u, rmax = (m.si >> 8) - lig * 16u;  // >= 16: another lane's
+            u32a* o = reinterpret_cast<u32a*>(mine);
+            wave_lds_sync();
+            if (rmin < 16u) o[small_piece(lane, rmin >> 2) * 4 + (rmin & 3u)] = m.sv << 16;
+            wave_lds_sync();  // both spikes in one slot (a malformed record): the maximum stays, as in the general kernel
+            if (rmax < 16u) o[small_piece(lane, rmax >> 2) * 4 + (rmax & 3u)] = m.sv & 0xFFFF0000u;
+        }
+    }
+    if ((meta_mode_out_arg & kZeroPadding) && blockIdx.x == 0 && wave == (blockDim.x >> 6) - 1u)
+        zero_padding<BITS, SR>(out, rec_out, n, n / G, meta_mode_out, lane);
+    __syncthreads();
+    constexpr int EPL = 8, LPG = G / EPL;
+    const uint32_t L8 = tile0 / EPL + threadIdx.x;
+    if (threadIdx.x >= kSmallTile / EPL || L8 >= n / EPL) return;
+    float acc[EPL];
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) acc[j] = -0.0f;
+    const uint32_t row = threadIdx.x >> 1, q0 = 2 * (threadIdx.x & 1);
+    const uint32_t at0 = small_piece(row, q0), at1 = small_piece(row, q0 + 1);
+    auto add = [&](const uint4& a, const uint4& b) {
+        const uint32_t x[EPL] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) acc[j] = __fadd_rn(acc[j], u2f(x[j]));
+    };
+    uint4 a[kSmallPeers], b[kSmallPeers];  // all peers' values first (peers beyond the last repeat it and are not added)
+#pragma unroll
+    for (int p = 0; p < (int)kSmallPeers; ++p) {
+        const uint4* from = vals + min(p, n_peers - 1) * (int)(kSmallTile / 4);
+        a[p] = from[at0];
+        b[p] = from[at1];
+    }
+#pragma unroll
+    for (int p = 0; p < (int)kSmallPeers; ++p)
+        if (p < n_peers) add(a[p], b[p]);
+    if (sum_out) {
+        float4* dst = reinterpret_cast<float4*>(sum_out) + (EPL / 4) * (uint64_t)L8;
+        dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    }
+    uint32_t w[EPL / 2];
+#pragma unroll
+    for (int d = 0; d < EPL / 2; ++d) w[d] = pack_bf16(acc[2 * d], acc[2 * d + 1]);
+    uint32_t c[EPL / 4];
+    GroupMeta m;
+    const uint32_t lig = threadIdx.x & (LPG - 1);
+    // the lane's scratch: the pieces of its own elements of peer 0, which nothing else reads
+    quantize_lane<BITS, EPL, LPG, SR>(w, lig, meta_mode_out, tabs, vals + at0, c, m);
+    store_planes<BITS, EPL>(out, rec_out, L8, c);
+    if (lig == 0) store_meta<SR>(out, rec_out, L8 / LPG, m, meta_mode_out);
+}
+
 // The same step when the peers' bit width differs from the output's: the input width is a run-time value
 // (one uniform switch around the peer loop), the output width stays a template parameter.  A compatibility path next to
 // the specialised kernel above: spikes always through the park, no choice of occupancy per width.
@@ -344,10 +457,25 @@ __global__ __launch_bounds__(kBlock) void k_reduce_requant_mixed(PeerPtrs peers,
 template <int BITS, int G, bool SR> struct LaunchReduce {
     static int run(const PeerPtrs& peers, int n_peers, uint64_t n, const Rec& rec_in, void* out, const Rec& rec_out,
                    float* sum_out, uint32_t mf_in, uint32_t mf_out, hipStream_t st) {
+        const bool im = mf_in == kMetaInt || (mf_out & 3u) == kMetaInt;
+        // Below a million elements the general kernel is less than one wave per SIMD and its time the chain of a wave through
+        // its peers; above it, values passing through LDS cost more than they save.  Measured on the MI355X, us per call,
+        // general -> small kernel: 3 bits of 64 x 7168 with 8 / 5 / 3 peers 6.2 -> 4.0, 5.2 -> 3.8, 4.4 -> 3.7; of 128 x 7168
+        // 6.2 -> 5.6, 5.2 -> 4.3, 4.4 -> 3.9; of 192 x 7168 6.9 -> 7.2, 5.7 -> 5.7, 4.7 -> 4.6.  Without spikes the chain is
+        // short: 8 bits of 64 x 7168 with 5 peers 3.6 -> 3.3, of 146 x 7168 3.7 -> 3.8.  One peer is no chain (3.3 -> 3.4).
+        if (n <= (SR ? 1u << 20 : 1u << 19) && n_peers >= 2 && n_peers <= (int)kSmallPeers) {
+            const dim3 grid((unsigned)((n + kSmallTile - 1) / kSmallTile)), block(64 * (unsigned)n_peers);
+            const size_t lds = (size_t)n_peers * kSmallTile * 4;
+            if (im)
+                return launch(k_reduce_small<BITS, G, SR, true>, grid, block, lds, st, peers, n_peers, (uint32_t)n, rec_in, (uint8_t*)out,
+                              rec_out, sum_out, mf_in, mf_out);
+            return launch(k_reduce_small<BITS, G, SR, false>, grid, block, lds, st, peers, n_peers, (uint32_t)n, rec_in, (uint8_t*)out, rec_out,
+                          sum_out, mf_in, mf_out);
+        }
         constexpr int EPL = FCV2_REDUCE_EPL(G);
         constexpr int PATCH = FCV2_REDUCE_PATCH(BITS);
         const uint32_t n_lanes = (uint32_t)(n / EPL);
-        const size_t tab_bytes = (mf_in == kMetaInt || (mf_out & 3u) == kMetaInt) ? sizeof(float) * kScaleTables : 0;
+        const size_t tab_bytes = im ? sizeof(float) * kScaleTables : 0;
         return launch(k_reduce_requant<BITS, EPL, G / EPL, SR, PATCH>, dim3(grid_lanes_xcd(n_lanes)), dim3(kBlock), tab_bytes, st, peers,
                       n_peers, n_lanes, rec_in, (uint8_t*)out, rec_out, sum_out, mf_in, mf_out);
     }
