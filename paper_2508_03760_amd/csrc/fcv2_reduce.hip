@@ -193,6 +193,30 @@ __device__ __forceinline__ void add_peer_values(const RawPlanes<EPL>& r, const G
     }
 }
 
+// The sums of a wave's lanes, 64 bytes each, through the lanes' LDS rows into stores that cover whole lines: written from the lanes
+// directly, a store instruction would touch a quarter of each of 32 lines.
+// Measured on the MI355X (buffers not in the last-level cache, us per call, direct -> through LDS, with the non-temporal hint):
+// 3.2 M elements of 5 peers at 8 bits 11.2 -> 8.4, 16 M of 8 at 3 bits 43.3 -> 35.3, 16 M of 4 at 8 bits 41.0 -> 31.5.
+template <int EPL, int ROW> __device__ __forceinline__ void store_sums(float* sum_out, uint4* lds, uint32_t L, uint32_t n_lanes, const float (&acc)[EPL]) {
+    const uint32_t lane = threadIdx.x & 63, first = threadIdx.x - lane, L0 = L - lane;
+    const uint32_t here = min(64u, n_lanes - L0);  // lanes of the wave that have elements: the first ones
+    uint8_t* dst = reinterpret_cast<uint8_t*>(sum_out) + (uint64_t)L0 * (EPL * 4);
+#pragma unroll
+    for (int h = 0; h < EPL / 16; ++h) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            lds[threadIdx.x * ROW + i] = make_uint4(f2u(acc[16 * h + 4 * i]), f2u(acc[16 * h + 4 * i + 1]), f2u(acc[16 * h + 4 * i + 2]),
+                                                    f2u(acc[16 * h + 4 * i + 3]));
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t piece = k * here + lane, r = piece >> 2, q = piece & 3u;
+            store_stream(dst + (r * (EPL * 4) + 64 * h + 16 * q), lds[(first + r) * ROW + q]);
+        }
+        wave_lds_sync();
+    }
+}
+
 template <int BITS, int EPL, int LPG, bool SR, int PATCH>
 // Peers are taken two at a time (both peers' loads issued before either is decoded).  Every peer in flight costs
 // about 15 registers; with two the kernel needs 65 to 74 and six or seven waves fit a SIMD, which measured faster
@@ -255,11 +279,7 @@ void k_reduce_requant(PeerPtrs peers, int n_peers, uint32_t n_lanes, Rec rec_in,
         sum_peers(std::true_type{});
     else
         sum_peers(std::false_type{});
-    if (sum_out) {
-        float4* dst = reinterpret_cast<float4*>(sum_out) + (EPL / 4) * (uint64_t)L;
-#pragma unroll
-        for (int i = 0; i < EPL / 4; ++i) dst[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
-    }
+    if (sum_out) store_sums<EPL, ROW>(sum_out, lds, L, n_lanes, acc);
     uint32_t w[EPL / 2];
 #pragma unroll
     for (int d = 0; d < EPL / 2; ++d) w[d] = pack_bf16(acc[2 * d], acc[2 * d + 1]);
@@ -439,11 +459,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_requant_mixed(PeerPtrs peers,
         case 7: sum_peers(std::integral_constant<int, 7>{}); break;
         default: sum_peers(std::integral_constant<int, 8>{}); break;
     }
-    if (sum_out) {
-        float4* dst = reinterpret_cast<float4*>(sum_out) + (EPL / 4) * (uint64_t)L;
-#pragma unroll
-        for (int i = 0; i < EPL / 4; ++i) dst[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
-    }
+    if (sum_out) store_sums<EPL, ROW>(sum_out, lds, L, n_lanes, acc);
     uint32_t w[EPL / 2];
 #pragma unroll
     for (int d = 0; d < EPL / 2; ++d) w[d] = pack_bf16(acc[2 * d], acc[2 * d + 1]);
