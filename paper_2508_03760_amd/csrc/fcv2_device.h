@@ -811,6 +811,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 constexpr int kRowU4 = 4;  // uint4 per lane row
 __device__ __forceinline__ uint32_t tile_slot(uint32_t row, uint32_t q) { return row * kRowU4 + (q ^ ((row >> 1) & 3u)); }
 
+// The same for the two 16-byte halves of a lane's 32 codes of 8 bits: slot q of row r at 2r + (q ^ ((r >> 2) & 1)).
+__device__ __forceinline__ uint32_t half_row_slot(uint32_t row, uint32_t q) { return row * 2 + (q ^ ((row >> 2) & 1u)); }
+
 struct TileIn {
     uint4 piece[4];
 };
