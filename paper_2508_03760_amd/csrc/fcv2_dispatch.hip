@@ -7,7 +7,7 @@ namespace fcv2 {
 
 // ---- dispatch: stable counting sort of the routed copies by expert, then quantize-and-scatter ------------------------
 // No order-dependent atomics, no waiting between blocks.  Small routings are one launch, the quantize-and-scatter kernel
-// planning for itself (self_planned, plan_block); otherwise three:
+// planning for itself (self_planned, plan_block); middle-sized ones two (ranked_plan, k_dispatch_rank); otherwise three:
 //   1. k_dispatch_count_rank   per chunk of 256 routed slots: the chunk's histogram over the experts, and for every slot
 //                              its stable rank among the chunk's slots of the same expert (one byte);
 //   2. k_dispatch_scan_chunks  per expert: exclusive prefix of the histograms over the chunks (in place) and the total;
@@ -150,6 +150,77 @@ __global__ __launch_bounds__(64) void k_dispatch_scan_chunks(int32_t* __restrict
     }
 }
 
+// The plan of middle-sized routings in one launch: block e goes through all ids, which stay in registers (16 per thread),
+// and writes rank[i], the number of earlier slots of expert e, for every slot i of that expert, and totals[e].  A wave
+// counts with ballots; the counts of (step, wave) are scanned by one wave; matches, one in E, are ranked in a second pass over the
+// registers.  ids are 16-byte aligned and fill at least one step.
+constexpr uint32_t kRankThreads = 1024, kRankSteps = 4;
+__global__ __launch_bounds__(kRankThreads) void k_dispatch_rank(const int32_t* __restrict__ ids, uint32_t n_slots, int32_t* __restrict__ totals,
+                                                                int32_t* __restrict__ rank) {
+    constexpr uint32_t W = kRankThreads / 64, KMAX = kRankSteps;
+    __shared__ uint32_t before[KMAX * W];  // [step][wave]: the counts, then their exclusive sums
+    const int32_t mine = (int32_t)blockIdx.x;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int4* ids4 = reinterpret_cast<const int4*>(ids);
+    const uint32_t n4 = n_slots >> 2;
+    int4 e[KMAX];
+#pragma unroll
+    for (uint32_t k = 0; k < KMAX; ++k) e[k] = ids4[min(k * kRankThreads + threadIdx.x, n4 - 1u)];
+    uint64_t m[4];
+    auto matches = [&](uint32_t k) {
+        const bool in = k * kRankThreads + threadIdx.x < n4;
+        m[0] = __ballot(in && e[k].x == mine);
+        m[1] = __ballot(in && e[k].y == mine);
+        m[2] = __ballot(in && e[k].z == mine);
+        m[3] = __ballot(in && e[k].w == mine);
+    };
+#pragma unroll
+    for (uint32_t k = 0; k < KMAX; ++k) {
+        matches(k);
+        if (lane == 0) before[k * W + wave] = __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        constexpr uint32_t PER = KMAX * W / 64;
+        uint32_t c[PER], sum = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j) {
+            c[j] = before[lane * PER + j];
+            sum += c[j];
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t up = __shfl_up(inc, d);
+            if ((int)lane >= d) inc += up;
+        }
+        uint32_t run = inc - sum;
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j) {
+            before[lane * PER + j] = run;
+            run += c[j];
+        }
+        if (lane == 63) {  // the last zero to three slots, and the total
+            for (uint32_t i = 4 * n4; i < n_slots; ++i)
+                if (ids[i] == mine) rank[i] = (int32_t)inc++;
+            totals[mine] = (int32_t)inc;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < KMAX; ++k) {
+        matches(k);
+        if ((m[0] | m[1] | m[2] | m[3]) == 0) continue;  // uniform in the wave
+        uint32_t r = before[k * W + wave];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r += __builtin_amdgcn_mbcnt_hi((uint32_t)(m[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[j], 0u));
+        int32_t* at = rank + 4 * (k * kRankThreads + threadIdx.x);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if ((m[j] >> lane) & 1u) at[j] = (int32_t)r++;
+    }
+}
+
 // Expert starts (exclusive scan of the totals) into start[0..E), by the whole block, in two steps so that a caller can put
 // other loads between them: the thread's share of the totals is read and summed first, the scan follows.  The second
 // step returns the number of routed copies and ends with a barrier: start[] is complete for every thread.
@@ -286,13 +357,18 @@ constexpr int kRowsBlockMax = 512;  // threads of the row-staged kernel (8 waves
 // Row-staged kernel.  A block owns `rows_per_block` consecutive tokens (blockDim = their lanes rounded up to whole waves,
 // chosen on the host: the count up to 64 that leaves the fewest idle lanes; 1 and 2 rows measure the same at H = 7168).
 // Dynamic LDS: per wave the transpose scratch | the records | the destination rows | the tables.
+constexpr uint32_t kPlanChunks = 0;  // k_dispatch_count_rank and k_dispatch_scan_chunks: hist, lrank, totals
+constexpr uint32_t kPlanRanked = 1;  // k_dispatch_rank: rank, totals
+constexpr uint32_t kPlanSelf = 2;    // no launch before this one (plan_block)
 struct DispatchPlan {  // what the planning launches left in the workspace, and the two index outputs of the call
     const int32_t* ids;
-    const int32_t* hist;  // null: no planning launches ran, every block plans for itself (self_planned)
+    const int32_t* hist;
     const int32_t* totals;
     const uint8_t* lrank;
+    const int32_t* rank;  // kPlanRanked only (otherwise anything that may be read at a slot's index)
     int32_t* expert_offsets;
     int32_t* row_src;
+    uint32_t mode;  // who planned: kPlanChunks, kPlanRanked, kPlanSelf
     uint32_t E;
     uint32_t totals_last;  // last entry of totals that may be read
     uint32_t fresh_rows;  // T * K when send buffer and row_src hold no values yet (fcv2_fresh.h), else 0
@@ -418,7 +494,8 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
     int32_t tot[4];  // up to 256 experts: the lane's totals, four independent loads
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) tot[k] = plan.totals[min(e0 + k, plan.totals_last)];
-    const bool self = plan.hist == nullptr;
+    const int32_t my_ranked = plan.rank[min(my_slot, T * K - 1u)];
+    const bool self = plan.mode == kPlanSelf;
     const bool has_tile = wave * 64 < block_lanes;  // whole waves past the block's last row only help with the copies
     TileIn in = {};
     if (has_tile) in = tile_load(x, (row0 * lanes_per_row + wave * 64) * 4, lane, (block_lanes - wave * 64) * 4);
@@ -467,7 +544,9 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
         for (uint32_t t = threadIdx.x; t < (uint32_t)kScaleTables; t += blockDim.x) tabs[t] = kScaleTablesInit.v[t];
     }
     __syncthreads();
-    if (!self && my_e >= 0) {
+    if (plan.mode == kPlanRanked) {
+        my_rank = my_ranked;
+    } else if (!self && my_e >= 0) {
         my_before = plan.hist[(uint64_t)(my_slot / kChunk) * plan.E + my_e];
         my_rank = (int32_t)plan.lrank[my_slot];
     }
@@ -491,7 +570,13 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
     }
     for (uint32_t i = threadIdx.x + blockDim.x; i < n_slots_here; i += blockDim.x) {  // more routed slots than threads: rare
         const uint32_t slot = row0 * K + i;
-        const int32_t r = dest_row_of(slot, plan.ids, plan.E, plan.hist, plan.lrank, start);
+        int32_t r;
+        if (plan.mode == kPlanRanked) {
+            const int32_t e = plan.ids[slot];
+            r = (uint32_t)e < plan.E ? start[e] + plan.rank[slot] : -1;
+        } else {
+            r = dest_row_of(slot, plan.ids, plan.E, plan.hist, plan.lrank, start);
+        }
         drow[i] = r;
         if (r >= 0) plan.row_src[r] = (int32_t)slot;
     }
@@ -616,6 +701,14 @@ static bool self_planned(const RowsPlan& rp, const int32_t* ids, uint32_t T, uin
     return n_slots <= 8192u && n_slots * blocks <= (1u << 23);
 }
 
+// Whether one launch ranks all slots (k_dispatch_rank) where two would count and scan chunks.  A block per expert reads every id, so
+// the work grows with slots x experts.  Measured on the MI355X (us per call, two launches -> one): 2048 tokens of 4096 elements x 4 on
+// 64 experts 15.7 -> 13.9, 2048 x 7168 x 8 on 256 24.0 -> 22.8, 8192 x 1024 x 1 on 16 13.4 -> 12.4; with four times the registers
+// for more slots 4096 x 1024 x 8 on 256 17.0 -> 19.8, 8192 x 7168 x 8 80.6 -> 86.7.
+static bool ranked_plan(const RowsPlan& rp, const int32_t* ids, uint32_t n_slots, uint32_t E) {
+    return rp.rows != 0 && (reinterpret_cast<uintptr_t>(ids) & 15u) == 0 && n_slots >= 4 && n_slots <= 4 * kRankThreads * kRankSteps && E <= 256u;
+}
+
 int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, uint32_t T, uint32_t H, uint32_t K, uint32_t E,
                     uint8_t* send, int32_t* expert_offsets, int32_t* row_src, void* ws, const Rec& rec, uint32_t row_bytes,
                     bool fresh, hipStream_t st) {
@@ -626,7 +719,12 @@ int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, ui
     int32_t* dest = (int32_t*)((uint8_t*)ws + w.off_dest);
     const RowsPlan rp = rows_plan(H / kEplStream, K, row_bytes, meta_mode_of(fmt) == kMetaInt, E);
     if (self_planned(rp, ids, T, K, E)) {
-        const DispatchPlan plan = {ids, nullptr, ids, nullptr, expert_offsets, row_src, E, 0u, fresh ? w.n_slots : 0u};
+        const DispatchPlan plan = {ids, nullptr, ids, nullptr, ids, expert_offsets, row_src, kPlanSelf, E, 0u, fresh ? w.n_slots : 0u};
+        return by_format<LaunchDispatch>(fmt, x, T, H, K, plan, dest, send, rec, row_bytes, meta_mode_of(fmt), st);
+    }
+    if (ranked_plan(rp, ids, w.n_slots, E)) {
+        if (launch(k_dispatch_rank, dim3(E), dim3(kRankThreads), 0, st, ids, w.n_slots, totals, dest) != FCV2_OK) return FCV2_ERR_LAUNCH;
+        const DispatchPlan plan = {ids, nullptr, totals, nullptr, dest, expert_offsets, row_src, kPlanRanked, E, E - 1u, fresh ? w.n_slots : 0u};
         return by_format<LaunchDispatch>(fmt, x, T, H, K, plan, dest, send, rec, row_bytes, meta_mode_of(fmt), st);
     }
     const size_t mask_bytes = (size_t)(kChunk / 64) * E * 8;  // lane masks per wave and expert: 8 KiB at 256 experts
@@ -635,7 +733,7 @@ int launch_dispatch(const fcv2_fmt_t* fmt, const void* x, const int32_t* ids, ui
                        : launch(k_dispatch_count_rank<false>, dim3(w.n_chunks), dim3(kChunk), mask_bytes / 2, st, ids, w.n_slots, E, hist, lrank);
     if (rc != FCV2_OK) return FCV2_ERR_LAUNCH;
     if (launch(k_dispatch_scan_chunks, dim3(E), dim3(64), 0, st, hist, w.n_chunks, E, totals) != FCV2_OK) return FCV2_ERR_LAUNCH;
-    const DispatchPlan plan = {ids, hist, totals, lrank, expert_offsets, row_src, E, E - 1u, fresh ? w.n_slots : 0u};
+    const DispatchPlan plan = {ids, hist, totals, lrank, ids, expert_offsets, row_src, kPlanChunks, E, E - 1u, fresh ? w.n_slots : 0u};
     return by_format<LaunchDispatch>(fmt, x, T, H, K, plan, dest, send, rec, row_bytes, meta_mode_of(fmt), st);
 }
 

@@ -1,5 +1,5 @@
-"""Small routings, which the quantize-and-scatter kernel plans by itself, at the edges of that rule: against the oracle, and
-against the same call planned by its own launches (which ids that are not 16-byte aligned take)."""
+"""Routings that the quantize-and-scatter kernel plans by itself or after one ranking launch, at the edges of those rules: against
+the oracle, and against the same call planned in chunks (which ids that are not 16-byte aligned take)."""
 import numpy as np
 import pytest
 import torch
@@ -23,6 +23,8 @@ DEV = "cuda:0"
     (300, 256, 4, 16), (300, 128, 4, 16),    # 8 rows a block; 16 rows of 4 slots, the most a wave ranks
     (1500, 2560, 2, 8),                      # many slots of few experts
     (257, 16384, 8, 2),                      # eight waves a block
+    (2731, 256, 3, 5), (2048, 256, 8, 40), (2049, 256, 8, 40),  # ranked by one launch: a slot left over, 4 full steps, one slot more than that
+    (4096, 256, 4, 256), (4097, 256, 4, 256), (4096, 256, 4, 257),  # the most slots and experts that are
 ])
 @pytest.mark.parametrize("fmt", [(4, 32, SR), (2, 128, SR | INT)])
 def test_both_plans_match_the_oracle(T, H, K, E, fmt):
