@@ -460,7 +460,9 @@ __device__ __forceinline__ uint32_t plan_block(const DispatchPlan& plan, uint32_
     return rank;
 }
 
-template <int BITS, int LPG, bool SR, bool INT_META>
+// CHUNKS: planned by kPlanChunks; else by one of the other two, a branch on plan.mode.  With all three behind run-time branches the
+// largest routings paid 0.5 us of 60.
+template <int BITS, int LPG, bool SR, bool INT_META, bool CHUNKS>
 __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* __restrict__ x, uint32_t T, uint32_t lanes_per_row,
                                                                   uint32_t K, DispatchPlan plan, uint8_t* __restrict__ send, Rec rec,
                                                                   uint32_t row_bytes, uint32_t meta_mode_arg, uint32_t rows_per_block) {
@@ -493,9 +495,9 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
     const uint32_t e0 = min(lane * per, plan.E), e1 = min(e0 + per, plan.E);
     int32_t tot[4];  // up to 256 experts: the lane's totals, four independent loads
 #pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) tot[k] = plan.totals[min(e0 + k, plan.totals_last)];
-    const int32_t my_ranked = plan.rank[min(my_slot, T * K - 1u)];
-    const bool self = plan.mode == kPlanSelf;
+    for (uint32_t k = 0; k < 4; ++k) tot[k] = plan.totals[min(e0 + k, CHUNKS ? plan.E - 1u : plan.totals_last)];
+    const int32_t my_ranked = CHUNKS ? 0 : plan.rank[min(my_slot, T * K - 1u)];
+    const bool self = !CHUNKS && plan.mode == kPlanSelf;
     const bool has_tile = wave * 64 < block_lanes;  // whole waves past the block's last row only help with the copies
     TileIn in = {};
     if (has_tile) in = tile_load(x, (row0 * lanes_per_row + wave * 64) * 4, lane, (block_lanes - wave * 64) * 4);
@@ -544,9 +546,9 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
         for (uint32_t t = threadIdx.x; t < (uint32_t)kScaleTables; t += blockDim.x) tabs[t] = kScaleTablesInit.v[t];
     }
     __syncthreads();
-    if (plan.mode == kPlanRanked) {
-        my_rank = my_ranked;
-    } else if (!self && my_e >= 0) {
+    if (!CHUNKS) {
+        if (!self) my_rank = my_ranked;
+    } else if (my_e >= 0) {
         my_before = plan.hist[(uint64_t)(my_slot / kChunk) * plan.E + my_e];
         my_rank = (int32_t)plan.lrank[my_slot];
     }
@@ -571,7 +573,7 @@ __global__ __launch_bounds__(kRowsBlockMax) void k_dispatch_rows_t(const uint4* 
     for (uint32_t i = threadIdx.x + blockDim.x; i < n_slots_here; i += blockDim.x) {  // more routed slots than threads: rare
         const uint32_t slot = row0 * K + i;
         int32_t r;
-        if (plan.mode == kPlanRanked) {
+        if (!CHUNKS) {  // ranked: a block that plans for itself has no more slots than threads
             const int32_t e = plan.ids[slot];
             r = (uint32_t)e < plan.E ? start[e] + plan.rank[slot] : -1;
         } else {
@@ -665,11 +667,12 @@ template <int BITS, int G, bool SR> struct LaunchDispatch {
         const RowsPlan rp = rows_plan(lpr, K, row_bytes, im, plan.E);
         if (rp.rows) {
             const dim3 grid((T + rp.rows - 1) / rp.rows), block(rp.threads);
-            if (im)
-                return launch(k_dispatch_rows_t<BITS, LPG, SR, true>, grid, block, rp.lds_bytes, st, (const uint4*)x, T, lpr, K, plan, send,
-                              rec, row_bytes, meta_mode, rp.rows);
-            return launch(k_dispatch_rows_t<BITS, LPG, SR, false>, grid, block, rp.lds_bytes, st, (const uint4*)x, T, lpr, K, plan, send, rec,
-                          row_bytes, meta_mode, rp.rows);
+            auto rows = [&](auto kernel) {
+                return launch(kernel, grid, block, rp.lds_bytes, st, (const uint4*)x, T, lpr, K, plan, send, rec, row_bytes, meta_mode, rp.rows);
+            };
+            if (plan.mode == kPlanChunks)
+                return im ? rows(k_dispatch_rows_t<BITS, LPG, SR, true, true>) : rows(k_dispatch_rows_t<BITS, LPG, SR, false, true>);
+            return im ? rows(k_dispatch_rows_t<BITS, LPG, SR, true, false>) : rows(k_dispatch_rows_t<BITS, LPG, SR, false, false>);
         }
         // Row shapes the staged kernel cannot take: destination rows written out by one more small launch, then the direct kernel.
         const uint32_t n_slots = T * K;
