@@ -5,6 +5,8 @@
 // MI355X (16 M-element payload, 8 peers, inputs not in the last-level cache, us per launch, runs on one machine):
 //   at 2 / 3 / 4 / 5 / 6 / 7 / 8 bits, 16 elements per lane: overlay at 2 and 3 bits and park above (the choice below)
 //   26.2 / 28.3 / 27.7 / 32.2 / 32.5 / 38.3 / 34.1; park everywhere 26.6 / 28.2 / 27.7 / 32.3 / 32.4 / 38.2 / 34.1;
+//   (5 to 7 bits before their codes were joined in place; since then, groups of 128, on another machine 25.4 / 28.2 / 27.2 /
+//   31.1 / 32.1 / 35.8 / 33.1, overlay everywhere 24.9 / 28.1 / 27.4 / 32.2 / 33.0 / 37.2 / 34.0);
 //   32 elements per lane (112 registers, four waves per SIMD; five spill): within 1 us of 16 at every width, not better;
 //   one peer in flight at eight waves 29.7 at 3 bits, two at seven waves 28.5, the next two peers requested under the
 //   decoding of the current two 29.6 (against 28.8 in that run).
