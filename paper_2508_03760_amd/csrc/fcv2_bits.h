@@ -1,9 +1,9 @@
-// fcv2_bits.h -- integer building blocks of the codec kernels: bf16 bit handling, order keys, and the
+// fcv2_bits.h -- building blocks of the codec kernels: bf16 bit handling, order keys, a lane's part of the spike selection, and the
 // shift/mask sequences that move code fields between "one code per byte" registers and the packed bit planes
 // (Section 3.2 of arxiv 2508.03760: a b-bit code is split into 4/2/1-bit planes stored separately).
 //
-// Everything here is plain 32-bit integer arithmetic, usable from host and device, so the sequences can be
-// unit-tested on the CPU.  A lane of the kernels always works on 8 consecutive elements:
+// Everything here works inside one lane, on 32-bit integers and fp32 numbers, and is usable from host and device, so the
+// sequences can be unit-tested on the CPU.  The plane sequences work on 8 consecutive elements:
 //   c0 = codes of elements 0..3, one per byte (element 0 in bits 0..7), c1 = elements 4..7.
 #pragma once
 #include <math.h>
@@ -68,6 +68,54 @@ FCV2_D uint32_t or_and(uint32_t a, uint32_t b, uint32_t m) { return __builtin_am
 // sum of byte products: a.b0 * w.b0 + ... + a.b3 * w.b3 + c
 FCV2_D uint32_t dot4_u8(uint32_t a, uint32_t w, uint32_t c) { return __builtin_amdgcn_udot4(a, w, c, false); }
 FCV2_D uint32_t rotr32(uint32_t x, int r) { return __builtin_amdgcn_alignbit(x, x, r); }
+FCV2_D uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+FCV2_D uint32_t umin3(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_min3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+#define FCV2_F32_OP3(name, op)                                            \
+    FCV2_D float name(float a, float b, float c) {                        \
+        float r;                                                          \
+        asm(op " %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));     \
+        return r;                                                         \
+    }
+#define FCV2_F32_OP2(name, op)                                            \
+    FCV2_D float name(float a, float b) {                                 \
+        float r;                                                          \
+        asm(op " %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));                 \
+        return r;                                                         \
+    }
+FCV2_F32_OP3(f_med3, "v_med3_f32")
+FCV2_F32_OP3(f_minimum3, "v_minimum3_f32")  // these two return NaN if any operand is one
+FCV2_F32_OP3(f_maximum3, "v_maximum3_f32")
+FCV2_F32_OP2(f_min, "v_min_f32")
+FCV2_F32_OP2(f_max, "v_max_f32")
+#undef FCV2_F32_OP3
+#undef FCV2_F32_OP2
+// (sign | flip) ^ w, sign = the sign bit of each 16-bit half spread over it: one three-register bitwise operation.
+FCV2_D uint32_t keys_of_pair(uint32_t w, uint32_t key_flip) {
+    typedef short short2v __attribute__((ext_vector_type(2)));
+    const uint32_t sign = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2v, w) >> (short2v){15, 15});
+    return __builtin_amdgcn_bitop3_b32(sign, w, key_flip, 0x36);
+}
+// The low (high) bf16 half of w with position p below it, as an fp32 number.  Single instructions, opaque to the compiler: it would
+// keep the shifted and masked halves of all elements in registers from here to the quantizer, which takes the same halves (50
+// registers more, two waves per SIMD fewer).
+FCV2_D float composite_lo(uint32_t w, uint32_t p) {
+    float x;
+    asm("v_lshl_or_b32 %0, %1, 16, %2" : "=v"(x) : "v"(w), "i"(p));
+    return x;
+}
+FCV2_D float composite_hi(uint32_t w, uint32_t hi_mask, uint32_t p) {
+    float y;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(y) : "v"(w), "v"(hi_mask), "i"(p));
+    return y;
+}
 #else  // the host pass of the HIP compiler, and the CPU test build
 template <uint32_t C> FCV2_HD uint32_t and_lit(uint32_t x) { return x & C; }
 template <uint32_t C> FCV2_HD uint32_t xor_lit(uint32_t x) { return x ^ C; }
@@ -79,6 +127,24 @@ FCV2_HD uint32_t dot4_u8(uint32_t a, uint32_t w, uint32_t c) {
     return c;
 }
 FCV2_HD uint32_t rotr32(uint32_t x, int r) { return (x >> r) | (x << ((32 - r) & 31)); }
+FCV2_HD uint32_t umin3(uint32_t a, uint32_t b, uint32_t c) { return a < b ? (a < c ? a : c) : (b < c ? b : c); }
+FCV2_HD uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
+    const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
+    return c < lo ? lo : c > hi ? hi : c;
+}
+// -0 below +0, as the instructions have it; min and max of a number and a NaN are the number.
+FCV2_HD bool f_below(float a, float b) { return a < b || (a == b && signbit(a) && !signbit(b)); }
+FCV2_HD float f_min(float a, float b) { return a != a ? b : b != b ? a : f_below(b, a) ? b : a; }
+FCV2_HD float f_max(float a, float b) { return a != a ? b : b != b ? a : f_below(a, b) ? b : a; }
+FCV2_HD float f_minimum3(float a, float b, float c) { return (a != a || b != b || c != c) ? NAN : f_min(f_min(a, b), c); }
+FCV2_HD float f_maximum3(float a, float b, float c) { return (a != a || b != b || c != c) ? NAN : f_max(f_max(a, b), c); }
+FCV2_HD float f_med3(float a, float b, float c) { return f_max(f_min(a, b), f_min(f_max(a, b), c)); }
+FCV2_HD uint32_t keys_of_pair(uint32_t w, uint32_t key_flip) {
+    const uint32_t sign = ((w & 0x8000u) ? 0xFFFFu : 0u) | ((w & 0x80000000u) ? 0xFFFF0000u : 0u);
+    return (sign | key_flip) ^ w;
+}
+FCV2_HD float composite_lo(uint32_t w, uint32_t p) { return __builtin_bit_cast(float, (w << 16) | p); }
+FCV2_HD float composite_hi(uint32_t w, uint32_t hi_mask, uint32_t p) { return __builtin_bit_cast(float, (w & hi_mask) | p); }
 #endif
 
 // ---- plane structure of a b-bit code: widest plane first = most significant bits ---------------------------
@@ -104,6 +170,114 @@ FCV2_HD uint32_t bf16_rne_bits(uint32_t u) {
 
 // Smallest bf16-representable fp32 bit pattern that is >= the (positive, finite) input.
 FCV2_HD uint32_t bf16_round_up_bits(uint32_t u) { return (u + 0xFFFFu) & 0xFFFF0000u; }
+
+// ---- the spikes of a group: one lane's part (group_spikes puts the lanes together) -----------------------------------------
+FCV2_D float u2f(uint32_t u) { return __builtin_bit_cast(float, u); }
+FCV2_D uint32_t f2u(float f) { return __builtin_bit_cast(uint32_t, f); }
+
+// Order-preserving map of fp32 bit patterns to unsigned integers (-0 below +0).
+FCV2_D uint32_t key_of_f32(uint32_t x) { return x ^ ((uint32_t)((int32_t)x >> 31) | 0x80000000u); }
+
+// Running two smallest values (m1 <= m2) of a stream, two new values at a time: the new second smallest is the smaller
+// of the old one and the median of {m1, x, y} (m1 belongs to the three, so their median is the second smallest of the
+// three; whatever is second smallest overall is either that or the old m2).  Three instructions for two values.
+FCV2_D void push2_pair(uint32_t& m1, uint32_t& m2, uint32_t x, uint32_t y) {
+    const uint32_t t = umed3(m1, x, y);
+    m1 = umin3(m1, x, y);
+    m2 = m2 < t ? m2 : t;
+}
+
+// Two smallest composites (key << 16 | position) of the lane and two smallest of (~key << 16 | position), for any bit
+// patterns (NaN included).  Positions count inside the lane.
+template <int EPL> FCV2_D void lane_extremes_any(const uint32_t (&w)[EPL / 2], uint32_t& a1, uint32_t& a2, uint32_t& b1, uint32_t& b2) {
+    const uint32_t key_flip = vreg_const<0x80008000u>();
+#pragma unroll
+    for (int d = 0; d < EPL / 2; ++d) {
+        const uint32_t k = keys_of_pair(w[d], key_flip);
+        uint32_t e0 = (k << 16) | (uint32_t)(2 * d), e1 = (k & 0xFFFF0000u) | (uint32_t)(2 * d + 1);
+        FCV2_KEEP(e0);  // keeps each composite one shift-or / and-or instruction (no regrouping with the xor below)
+        FCV2_KEEP(e1);
+        const uint32_t f0 = xor_lit<0xFFFF0000u>(e0), f1 = xor_lit<0xFFFF0000u>(e1);  // inverted key: min finds the largest value
+        if (d == 0) {
+            a1 = e0 < e1 ? e0 : e1;
+            a2 = e0 < e1 ? e1 : e0;
+            b1 = f0 < f1 ? f0 : f1;
+            b2 = f0 < f1 ? f1 : f0;
+        } else {
+            push2_pair(a1, a2, e0, e1);
+            push2_pair(b1, b2, f0, f1);
+        }
+    }
+}
+
+// A bf16 value with a position in the 16 bits below it is an fp32 number, so the two smallest and two largest come out of the
+// fp32 median / minimum / maximum instructions: 8 instructions per pair of elements, where composites of integer order keys
+// (lane_extremes_any) take 12, half of them to build the keys and to invert them for the maximum.  The position stands there
+// inverted, so that of equal values the lowest index wins where the minimum is negative and the maximum is not; the other
+// way round (a group of one sign) the position is looked for again (lane_spikes_upright).  hi_mask = 0xFFFF0000.
+template <int EPL> FCV2_D void lane_spikes(const uint32_t (&w)[EPL / 2], uint32_t hi_mask, float& a1, float& a2, float& b1, float& b2) {
+#pragma unroll
+    for (int d = 0; d < EPL / 2; ++d) {
+        const float x = composite_lo(w[d], (uint32_t)(EPL - 1 - 2 * d)), y = composite_hi(w[d], hi_mask, (uint32_t)(EPL - 2 - 2 * d));
+        if (d == 0) {
+            a1 = f_minimum3(x, y, y);
+            a2 = f_max(x, y);
+            b1 = f_maximum3(x, y, y);
+            b2 = f_min(x, y);
+        } else {
+            const float ta = f_med3(a1, x, y), tb = f_med3(b1, x, y);
+            a1 = f_minimum3(a1, x, y);
+            b1 = f_maximum3(b1, x, y);
+            a2 = f_min(a2, ta);
+            b2 = f_max(b2, tb);
+        }
+    }
+}
+
+// The minimum and the two largest with the positions as they are.
+template <int EPL> FCV2_D void lane_spikes_upright(const uint32_t (&w)[EPL / 2], uint32_t hi_mask, float& a1, float& b1, float& b2) {
+#pragma unroll
+    for (int d = 0; d < EPL / 2; ++d) {
+        const float x = composite_lo(w[d], (uint32_t)(2 * d)), y = composite_hi(w[d], hi_mask, (uint32_t)(2 * d + 1));
+        if (d == 0) {
+            a1 = f_min(x, y);
+            b1 = f_max(x, y);
+            b2 = f_min(x, y);
+        } else {
+            const float t = f_med3(b1, x, y);
+            a1 = f_minimum3(a1, x, y);
+            b1 = f_maximum3(b1, x, y);
+            b2 = f_max(b2, t);
+        }
+    }
+}
+
+// Whether lane_spikes and lane_spikes_upright hold for the lane: no value is an infinity or a NaN.  With a position below it both
+// are NaNs, which minimum3 / maximum3 hand on to a1 and b1.  The one infinity that stays an infinity has position 0 below it,
+// that is the lane's last element in lane_spikes and its first in lane_spikes_upright; it then is the extreme of its side, so
+// looking for an infinity in a1 and b1 finds it too, before the second look makes it a NaN.
+FCV2_D bool spikes_are_finite(float a1, float b1) { return a1 > -INFINITY && b1 < INFINITY; }
+
+// What a lane found as integer composites (key << 16 | position in the group; the key inverted on the maximum's side).  The
+// inverted position of a negative number (of a non-negative one on the maximum's side) turns back here.
+template <int EPL> FCV2_D uint32_t spike_composite(float f, uint32_t lbase) {
+    return (key_of_f32(f2u(f)) & (0xFFFF0000u | (uint32_t)(EPL - 1))) | lbase;
+}
+template <int EPL> FCV2_D uint32_t spike_composite_inv(float f, uint32_t lbase) {
+    return (~key_of_f32(f2u(f)) & (0xFFFF0000u | (uint32_t)(EPL - 1))) | lbase;
+}
+
+// The group's minimum is +0 or above, or its maximum is negative: the positions of that side are still inverted.
+FCV2_D bool spikes_of_one_sign(uint32_t a1, uint32_t b1) { return (int32_t)(a1 | b1) < 0; }
+
+// ... and come from the second look (c1 the minimum, d1 and d2 the two largest) instead.
+FCV2_D void take_upright(uint32_t c1, uint32_t d1, uint32_t d2, uint32_t& a1, uint32_t& b1, uint32_t& b2) {
+    if ((int32_t)a1 < 0) a1 = c1;
+    if ((int32_t)b1 < 0) {
+        b1 = d1;
+        b2 = d2;
+    }
+}
 
 // d / QMAX with IEEE rounding for d >= 0, without the long division sequence: multiply by the rounded
 // reciprocal, then one exact-residual correction (Markstein).  Checked against IEEE division for every fp32

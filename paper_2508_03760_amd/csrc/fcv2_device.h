@@ -113,30 +113,6 @@ template <int K> __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
 typedef uint32_t __attribute__((may_alias)) u32a;
 typedef uint16_t __attribute__((may_alias)) u16a;
 
-__device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
-__device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
-
-__device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
-    uint32_t r;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-__device__ __forceinline__ uint32_t umin3(uint32_t a, uint32_t b, uint32_t c) {
-    uint32_t r;
-    asm("v_min3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-// Running two smallest values (m1 <= m2) of a stream, two new values at a time: the new second smallest is the smaller
-// of the old one and the median of {m1, x, y} (m1 belongs to the three, so their median is the second smallest of the
-// three; whatever is second smallest overall is either that or the old m2).  Three instructions for two values.
-__device__ __forceinline__ void push2_pair(uint32_t& m1, uint32_t& m2, uint32_t x, uint32_t y) {
-    const uint32_t t = umed3(m1, x, y);
-    m1 = umin3(m1, x, y);
-    m2 = min(m2, t);
-}
-
 // Two smallest values over the LPG lanes of a group (the lanes hold disjoint sets); all lanes get the result.
 template <int CTRL> __device__ __forceinline__ void merge2_step(uint32_t& m1, uint32_t& m2) {
     const uint32_t p1lo = (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFF, (int)m1, CTRL, 0xF, 0xF, false);
@@ -197,28 +173,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 }
 
 // ---- extremes of a group --------------------------------------------------------------------------------------------------
-// Order-preserving map of fp32 bit patterns to unsigned integers (-0 below +0).
-__device__ __forceinline__ uint32_t key_of_f32(uint32_t x) { return x ^ ((uint32_t)((int32_t)x >> 31) | 0x80000000u); }
-
-#define FCV2_F32_OP3(name, op)                                                                   \
-    __device__ __forceinline__ float name(float a, float b, float c) {                           \
-        float r;                                                                                 \
-        asm(op " %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));                            \
-        return r;                                                                                \
-    }
-#define FCV2_F32_OP2(name, op)                                                                   \
-    __device__ __forceinline__ float name(float a, float b) {                                    \
-        float r;                                                                                 \
-        asm(op " %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));                                        \
-        return r;                                                                                \
-    }
-FCV2_F32_OP3(f_med3, "v_med3_f32")
-FCV2_F32_OP3(f_minimum3, "v_minimum3_f32")  // these two return NaN if any operand is one
-FCV2_F32_OP3(f_maximum3, "v_maximum3_f32")
-FCV2_F32_OP2(f_min, "v_min_f32")
-FCV2_F32_OP2(f_max, "v_max_f32")
-#undef FCV2_F32_OP3
-#undef FCV2_F32_OP2
 __device__ __forceinline__ uint32_t pk_minimum3_f16(uint32_t a, uint32_t b, uint32_t c) {
     uint32_t r;
     asm("v_pk_minimum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
@@ -230,109 +184,29 @@ __device__ __forceinline__ uint32_t pk_maximum3_f16(uint32_t a, uint32_t b, uint
     return r;
 }
 
-// Order keys of the two bf16 halves of w: (sign | flip) ^ w, one three-register bitwise operation.
-__device__ __forceinline__ uint32_t keys_of_pair(uint32_t w, uint32_t key_flip) {
-    typedef short short2v __attribute__((ext_vector_type(2)));
-    const uint32_t sign = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2v, w) >> (short2v){15, 15});
-    return __builtin_amdgcn_bitop3_b32(sign, w, key_flip, 0x36);
-}
-
-// Two smallest composites (key << 16 | position) of the lane and two smallest of (~key << 16 | position), for any bit
-// patterns (NaN included).  Positions count inside the lane.
-template <int EPL> __device__ __forceinline__ void lane_extremes_any(const uint32_t (&w)[EPL / 2], uint32_t& a1, uint32_t& a2, uint32_t& b1,
-                                                                     uint32_t& b2) {
-    const uint32_t key_flip = vreg_const<0x80008000u>();
-#pragma unroll
-    for (int d = 0; d < EPL / 2; ++d) {
-        const uint32_t k = keys_of_pair(w[d], key_flip);
-        uint32_t e0 = (k << 16) | (uint32_t)(2 * d), e1 = (k & 0xFFFF0000u) | (uint32_t)(2 * d + 1);
-        FCV2_KEEP(e0);  // keeps each composite one shift-or / and-or instruction (no regrouping with the xor below)
-        FCV2_KEEP(e1);
-        const uint32_t f0 = xor_lit<0xFFFF0000u>(e0), f1 = xor_lit<0xFFFF0000u>(e1);  // inverted key: min finds the largest value
-        if (d == 0) {
-            a1 = min(e0, e1);
-            a2 = max(e0, e1);
-            b1 = min(f0, f1);
-            b2 = max(f0, f1);
-        } else {
-            push2_pair(a1, a2, e0, e1);
-            push2_pair(b1, b2, f0, f1);
-        }
-    }
-}
-
 // The two spikes of a group and the two next values (Section 3.3): composites of the minimum (a1), the second smallest (a2), the
-// maximum (b1, b2; key inverted) over the group, positions counted inside the group, lowest index on ties.
-//
-// A bf16 value with a position in the 16 bits below it is an fp32 number, so the two smallest and two largest come out of the
-// fp32 median / minimum / maximum instructions: 8 instructions per pair of elements, where composites of integer order keys
-// (lane_extremes_any) take 12, half of them to build the keys and to invert them for the maximum.  The position stands there
-// inverted, so that of equal values the lowest index wins where the minimum is negative and the maximum is not; the other
-// way round (a group of one sign) the position is looked for again.  NaN or infinite values (an infinity with a position
-// below it is a NaN) make minimum3 / maximum3 return NaN: the wave then takes the integer form.
+// maximum (b1, b2; key inverted) over the group, positions counted inside the group, lowest index on ties.  A lane's part is in
+// fcv2_bits.h (lane_spikes, lane_spikes_upright, and lane_extremes_any for a wave with an infinity or a NaN in it).
 template <int EPL, int LPG> __device__ __forceinline__ void group_spikes(const uint32_t (&w)[EPL / 2], uint32_t lbase, uint32_t& a1, uint32_t& a2,
                                                                          uint32_t& b1, uint32_t& b2) {
-    // Composites as single instructions, opaque to the compiler: it would keep the shifted and masked halves of all elements in
-    // registers from here to the quantizer, which takes the same halves (50 registers more, two waves per SIMD fewer).
     const uint32_t hi_mask = vreg_const<0xFFFF0000u>();
-    auto pair = [&](int d, bool inverted, float& x, float& y) {
-        const uint32_t p0 = inverted ? (uint32_t)(EPL - 1 - 2 * d) : (uint32_t)(2 * d), p1 = inverted ? p0 - 1u : p0 + 1u;
-        asm("v_lshl_or_b32 %0, %1, 16, %2" : "=v"(x) : "v"(w[d]), "i"(p0));
-        asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(y) : "v"(w[d]), "v"(hi_mask), "i"(p1));
-    };
     float fa1, fa2, fb1, fb2;
-#pragma unroll
-    for (int d = 0; d < EPL / 2; ++d) {
-        float x, y;
-        pair(d, true, x, y);
-        if (d == 0) {
-            fa1 = f_minimum3(x, y, y);
-            fa2 = f_max(x, y);
-            fb1 = f_maximum3(x, y, y);
-            fb2 = f_min(x, y);
-        } else {
-            const float ta = f_med3(fa1, x, y), tb = f_med3(fb1, x, y);
-            fa1 = f_minimum3(fa1, x, y);
-            fb1 = f_maximum3(fb1, x, y);
-            fa2 = f_min(fa2, ta);
-            fb2 = f_max(fb2, tb);
-        }
-    }
-    constexpr uint32_t kKeep = 0xFFFF0000u | (uint32_t)(EPL - 1);  // value and in-lane position
-    if (!__any(fa1 != fa1 || fb1 != fb1)) {
-        // as integers; the inverted position of a negative number (of a non-negative one on the maximum side) turns back
-        a1 = (key_of_f32(f2u(fa1)) & kKeep) | lbase;
-        a2 = (key_of_f32(f2u(fa2)) & kKeep) | lbase;
-        b1 = (~key_of_f32(f2u(fb1)) & kKeep) | lbase;
-        b2 = (~key_of_f32(f2u(fb2)) & kKeep) | lbase;
+    lane_spikes<EPL>(w, hi_mask, fa1, fa2, fb1, fb2);
+    if (!__any(!spikes_are_finite(fa1, fb1))) {
+        a1 = spike_composite<EPL>(fa1, lbase);
+        a2 = spike_composite<EPL>(fa2, lbase);
+        b1 = spike_composite_inv<EPL>(fb1, lbase);
+        b2 = spike_composite_inv<EPL>(fb2, lbase);
         group_min2<LPG>(a1, a2);
         group_min2<LPG>(b1, b2);
-        if (__any((int32_t)(a1 | b1) < 0)) {  // a minimum of +0 or above, or a negative maximum
+        if (__any(spikes_of_one_sign(a1, b1))) {
             float ga1, gb1, gb2;
-#pragma unroll
-            for (int d = 0; d < EPL / 2; ++d) {
-                float x, y;
-                pair(d, false, x, y);
-                if (d == 0) {
-                    ga1 = f_min(x, y);
-                    gb1 = f_max(x, y);
-                    gb2 = f_min(x, y);
-                } else {
-                    const float t = f_med3(gb1, x, y);
-                    ga1 = f_minimum3(ga1, x, y);
-                    gb1 = f_maximum3(gb1, x, y);
-                    gb2 = f_max(gb2, t);
-                }
-            }
-            uint32_t c1 = (key_of_f32(f2u(ga1)) & kKeep) | lbase;
-            uint32_t d1 = (~key_of_f32(f2u(gb1)) & kKeep) | lbase, d2 = (~key_of_f32(f2u(gb2)) & kKeep) | lbase;
+            lane_spikes_upright<EPL>(w, hi_mask, ga1, gb1, gb2);
+            uint32_t c1 = spike_composite<EPL>(ga1, lbase);
+            uint32_t d1 = spike_composite_inv<EPL>(gb1, lbase), d2 = spike_composite_inv<EPL>(gb2, lbase);
             c1 = group_min<LPG>(c1);
             group_min2<LPG>(d1, d2);
-            if ((int32_t)a1 < 0) a1 = c1;
-            if ((int32_t)b1 < 0) {
-                b1 = d1;
-                b2 = d2;
-            }
+            take_upright(c1, d1, d2, a1, b1, b2);
         }
     } else {
         lane_extremes_any<EPL>(w, a1, a2, b1, b2);

@@ -19,7 +19,7 @@ def build(force: bool = False, sanitize: bool = False) -> str:
     so = lib_path(sanitize)
     if not force and os.path.exists(so) and os.path.getmtime(so) >= max(os.path.getmtime(d) for d in DEPS):
         return so
-    cmd = ["g++", "-std=c++17", "-O1" if sanitize else "-O2", "-ffp-contract=off", "-fPIC", "-shared", "-Wall"]
+    cmd = ["g++", "-std=c++17", "-O1" if sanitize else "-O2", "-ffp-contract=off", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas"]
     cmd += (SANITIZE if sanitize else []) + ["-o", so + ".tmp", SRC]
     subprocess.run(cmd, check=True, cwd=HERE)
     os.replace(so + ".tmp", so)

@@ -67,7 +67,89 @@ template <int QMAX> static uint64_t div_mismatches(uint32_t first_bits, uint32_t
     return bad;
 }
 
+// group_spikes of fcv2_device.h over the 64 lanes of a wave, one loop over the lanes for each of its steps: x holds the wave's 64 * EPL
+// values, LPG lanes are a group; out4[lane] = the group's two smallest composites and, key inverted, its two largest.
+static void merge2(uint32_t& m1, uint32_t& m2, uint32_t p1, uint32_t p2) {  // the two smallest of two ordered pairs
+    const uint32_t t = m1 > p1 ? m1 : p1, u = m2 < p2 ? m2 : p2;
+    m1 = m1 < p1 ? m1 : p1;
+    m2 = t < u ? t : u;
+}
+template <int EPL> static void wave_spikes(const uint16_t* x, int lpg, int integers_only, uint32_t* out4) {
+    static thread_local uint32_t w[64][EPL / 2];
+    std::memcpy(w, x, sizeof(w));
+    auto over_groups = [&](uint32_t (*m)[64], bool second) {  // every lane gets what its group's lanes come to
+        for (int l = 0; l < 64; l += lpg) {
+            uint32_t m1 = m[0][l], m2 = second ? m[1][l] : ~0u;
+            for (int k = 1; k < lpg; ++k) merge2(m1, m2, m[0][l + k], second ? m[1][l + k] : ~0u);
+            for (int k = 0; k < lpg; ++k) {
+                m[0][l + k] = m1;
+                if (second) m[1][l + k] = m2;
+            }
+        }
+    };
+    uint32_t a[2][64], b[2][64];
+    float f[64][4];
+    bool finite = true;
+    for (int l = 0; l < 64; ++l) {
+        lane_spikes<EPL>(w[l], 0xFFFF0000u, f[l][0], f[l][1], f[l][2], f[l][3]);
+        finite = finite && spikes_are_finite(f[l][0], f[l][2]);
+    }
+    if (finite && !integers_only) {
+        bool one_sign = false;
+        for (int l = 0; l < 64; ++l) {
+            const uint32_t lbase = (uint32_t)(l % lpg) * EPL;
+            for (int k = 0; k < 2; ++k) {
+                a[k][l] = spike_composite<EPL>(f[l][k], lbase);
+                b[k][l] = spike_composite_inv<EPL>(f[l][2 + k], lbase);
+            }
+        }
+        over_groups(a, true);
+        over_groups(b, true);
+        for (int l = 0; l < 64; ++l) one_sign = one_sign || spikes_of_one_sign(a[0][l], b[0][l]);
+        if (one_sign) {
+            uint32_t c[1][64], d[2][64];
+            for (int l = 0; l < 64; ++l) {
+                const uint32_t lbase = (uint32_t)(l % lpg) * EPL;
+                float c1 = 0, d1 = 0, d2 = 0;
+                lane_spikes_upright<EPL>(w[l], 0xFFFF0000u, c1, d1, d2);
+                c[0][l] = spike_composite<EPL>(c1, lbase);
+                d[0][l] = spike_composite_inv<EPL>(d1, lbase);
+                d[1][l] = spike_composite_inv<EPL>(d2, lbase);
+            }
+            over_groups(c, false);
+            over_groups(d, true);
+            for (int l = 0; l < 64; ++l) take_upright(c[0][l], d[0][l], d[1][l], a[0][l], b[0][l], b[1][l]);
+        }
+    } else {
+        for (int l = 0; l < 64; ++l) {
+            const uint32_t lbase = (uint32_t)(l % lpg) * EPL;
+            lane_extremes_any<EPL>(w[l], a[0][l], a[1][l], b[0][l], b[1][l]);
+            for (int k = 0; k < 2; ++k) {
+                a[k][l] += lbase;
+                b[k][l] += lbase;
+            }
+        }
+        over_groups(a, true);
+        over_groups(b, true);
+    }
+    for (int l = 0; l < 64; ++l) {
+        out4[4 * l] = a[0][l];
+        out4[4 * l + 1] = a[1][l];
+        out4[4 * l + 2] = b[0][l];
+        out4[4 * l + 3] = b[1][l];
+    }
+}
+
 extern "C" {
+
+int hc_wave_spikes(int epl, const uint16_t* x, int lpg, int integers_only, uint32_t* out4) {
+    switch (epl) {
+        case 8: wave_spikes<8>(x, lpg, integers_only, out4); return 0;
+        case 16: wave_spikes<16>(x, lpg, integers_only, out4); return 0;
+        case 32: wave_spikes<32>(x, lpg, integers_only, out4); return 0;
+    }
+    return -1;
+}
 
 int hc_planes_of_codes(int bits, const uint8_t* codes, uint32_t* out5) {
     switch (bits) {

@@ -196,6 +196,73 @@ def test_bf16_helpers_match_oracle(hc):
         assert r >= u and r & 0xFFFF == 0 and r - u < 0x10000
 
 
+def _spike_groups(kind, ngroups, group, epl, rng):
+    """bf16 bit patterns of `ngroups` groups of one kind."""
+    z = rng.standard_normal((ngroups, group)).astype(np.float32)
+    at = np.arange(ngroups)
+    if kind.startswith("infinity"):  # in a group of one sign: at every position in turn, or at the last of a lane only
+        z = np.abs(z) + np.float32(0.5)
+        z[at, at * epl % group + epl - 1 if "last" in kind else at % group] = np.inf
+        if "ties" in kind:
+            z = np.where(np.isinf(z), z, np.round(z))
+        z *= np.float32(-1.0) if "negative" in kind else np.float32(1.0)
+    elif kind == "infinities of both signs":
+        z[at, at % group] = np.inf
+        z[at, (at * 7 + 3) % group] = -np.inf
+    elif kind in ("positive ties", "negative ties"):
+        z = np.round(np.abs(z) * 2) / 2 * (1.0 if kind[0] == "p" else -1.0)
+    elif kind == "zeros":
+        z = np.where(rng.random(z.shape) < 0.5, np.float32(0.0), np.float32(-0.0))
+    elif kind == "largest":
+        z = rng.choice(np.float32([3.3895e38, -3.3895e38, 1.0, -1.0]), size=z.shape)
+    u = (z.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    return rng.integers(0, 65536, u.shape).astype(np.uint16) if kind == "any bits" else u
+
+
+SPIKE_KINDS = ["normal", "infinity, positive", "infinity, negative", "infinity last, positive", "infinity last, negative",
+               "infinity last, positive ties", "infinity last, negative ties", "infinities of both signs", "positive ties", "negative ties",
+               "zeros", "largest", "any bits"]
+
+
+@pytest.mark.parametrize("epl", [8, 16, 32])
+@pytest.mark.parametrize("group", [32, 64, 128, 256])
+def test_spike_selection_is_the_integer_selection(hc, epl, group):
+    """The selection on fp32 composites against the one on integer keys and against a sort, over waves of one kind of groups and
+    of all kinds mixed (a wave takes one way for all its groups)."""
+    rng = np.random.default_rng(epl * 1000 + group)
+    lpg, per = group // epl, 64 * epl // group
+    rounds = max(8, 2 * group // per)
+    pools = {k: _spike_groups(k, rounds * per, group, epl, rng) for k in SPIKE_KINDS}
+    waves = [(k, p[r * per:(r + 1) * per]) for k, p in pools.items() for r in range(rounds)]
+    every = np.concatenate([pools[k] for k in SPIKE_KINDS if k != "any bits"])
+    plain = np.concatenate([pools[k] for k in SPIKE_KINDS if "infinit" not in k and k != "any bits"])
+    last = np.concatenate([plain] + [pools[k] for k in SPIKE_KINDS if "infinity last" in k])
+    waves += [("mixed", every[rng.integers(0, len(every), per)]) for _ in range(64)]
+    waves += [("mixed, finite", plain[rng.integers(0, len(plain), per)]) for _ in range(64)]
+    waves += [("mixed, infinities last", last[rng.integers(0, len(last), per)]) for _ in range(64)]
+
+    def select(x, integers_only):
+        out = np.zeros((64, 4), np.uint32)
+        x = np.ascontiguousarray(x)
+        assert hc.hc_wave_spikes(epl, x.ctypes.data_as(C.POINTER(C.c_uint16)), lpg, integers_only, out.ctypes.data_as(C.POINTER(C.c_uint32))) == 0
+        return out
+
+    for kind, x in waves:
+        got, want = select(x, 0), select(x, 1)
+        key = np.where(x & 0x8000, ~x, x | 0x8000).astype(np.uint32)
+        pos = np.arange(group, dtype=np.uint32)
+        by_sort = np.concatenate([np.sort((k << np.uint32(16)) | pos, axis=1)[:, :2] for k in (key, key ^ np.uint32(0xFFFF))], axis=1)
+        assert np.array_equal(want, np.repeat(by_sort, lpg, axis=0)), kind
+        # the quantizer reads: both spikes with their positions, the second smallest and second largest value, and the second largest's position in
+        # a constant group, where both first positions are the same
+        for lane in range(0, 64, lpg):
+            g, t = got[lane:lane + lpg], want[lane:lane + lpg]
+            assert np.array_equal(g[:, [0, 2]], t[:, [0, 2]]), kind
+            assert np.array_equal(g[:, [1, 3]] >> 16, t[:, [1, 3]] >> 16), kind
+            if t[0, 0] & 0xFFFF == t[0, 2] & 0xFFFF:
+                assert np.array_equal(g[:, 3], t[:, 3]), kind
+
+
 @pytest.mark.parametrize("qmax", [3, 7, 15, 31, 63, 127, 255])
 def test_short_division_is_ieee_division(hc, qmax):
     # every significand of one binade (scaling by powers of two is exact), plus the ranges where the exponent
