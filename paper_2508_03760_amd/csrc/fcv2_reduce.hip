@@ -51,7 +51,7 @@ namespace fcv2 {
 constexpr int kPatchPark = 0, kPatchOverlay = 1;
 
 // Which register of Q[8], and which half of it, holds element e of 16; by how much its code is shifted inside the half.
-template <int BITS> struct UnitPairMap {  // codes_pairs on two units of 8: unit u = Q[4u..4u+3], element k and k + 4, at bit 0
+struct UnitPairMap {  // codes_pairs_b8 on two units of 8: unit u = Q[4u..4u+3], element k and k + 4, at bit 0
     static constexpr int k_of(int e) { return 4 * (e >> 3) + (e & 3); }
     static constexpr bool in_hi(int e) { return ((e >> 2) & 1) != 0; }
     static constexpr int pos(int) { return 0; }
@@ -59,7 +59,7 @@ template <int BITS> struct UnitPairMap {  // codes_pairs on two units of 8: unit
 
 template <int BITS> struct PairCodes {
     static constexpr bool kInPlace = BITS <= 7;  // the fields are only masked, never moved to bit 0 (codes_pairs16)
-    using Map = typename std::conditional<kInPlace, PairMap<(kInPlace ? BITS : 2)>, UnitPairMap<BITS>>::type;
+    using Map = typename std::conditional<kInPlace, PairMap<(kInPlace ? BITS : 2)>, UnitPairMap>::type;
 };
 
 // The codes of half h (16 elements) of a lane's planes as pair registers.
@@ -73,7 +73,7 @@ template <int BITS, int EPL> __device__ __forceinline__ void pair_codes(const Ra
 #pragma unroll
         for (int uu = 0; uu < 2; ++uu) {
             uint32_t Q4[4];
-            codes_pairs<BITS>(r.p8[2 * (2 * h + uu)], r.p8[2 * (2 * h + uu) + 1], 0u, 0u, 0u, Q4);
+            codes_pairs_b8(r.p8[2 * (2 * h + uu)], r.p8[2 * (2 * h + uu) + 1], Q4);
 #pragma unroll
             for (int k = 0; k < 4; ++k) Q[4 * uu + k] = Q4[k];
         }

@@ -29,13 +29,26 @@ template <int BITS> static void codes_of_planes(uint32_t p4, uint32_t p2, uint32
     }
 }
 
+// 8 codes through the pair decoding that the width takes in the kernels: at 2 to 7 bits the one for 16 elements, of which the last
+// eight are 0 here.
 template <int BITS> static void pairs_of_planes(uint32_t p8lo, uint32_t p8hi, uint32_t p4, uint32_t p2, uint32_t p1, uint8_t* codes) {
-    uint32_t Q[4];
-    codes_pairs<BITS>(p8lo, p8hi, p4, p2, p1, Q);
-    for (int k = 0; k < 4; ++k) {
-        codes[k] = (uint8_t)(Q[k] & 0xFFFFu);
-        codes[k + 4] = (uint8_t)(Q[k] >> 16);
-        if ((Q[k] & 0xFF00FF00u) != 0) codes[k] = 0xEE;  // must be zero-extended
+    if constexpr (BITS == 8) {
+        uint32_t Q[4];
+        codes_pairs_b8(p8lo, p8hi, Q);
+        for (int k = 0; k < 4; ++k) {
+            codes[k] = (uint8_t)(Q[k] & 0xFFFFu);
+            codes[k + 4] = (uint8_t)(Q[k] >> 16);
+            if ((Q[k] & 0xFF00FF00u) != 0) codes[k] = 0xEE;  // must be zero-extended
+        }
+    } else {
+        using M = PairMap<BITS>;
+        uint32_t Q[8];
+        codes_pairs16<BITS>(p4, 0u, p2, p1, Q);
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t v = (M::in_hi(e) ? Q[M::k_of(e)] >> 16 : Q[M::k_of(e)] & 0xFFFFu) >> M::pos(M::k_of(e));
+            if (e < 8) codes[e] = (uint8_t)v;
+            if (v >> (e < 8 ? BITS : 0)) codes[e & 7] = 0xEE;  // nothing above a code, nothing where there is none
+        }
     }
 }
 
