@@ -56,8 +56,7 @@ constexpr uint32_t kZeroPadding = 4;
 // them leaves the kernel; tabs holds kScaleTablePow + kScaleTableThr floats.
 constexpr int kScaleTables = kScaleTablePow + kScaleTableThr;
 __device__ __forceinline__ void fill_scale_tables(float* tabs) {
-    // a plain copy of the compile-time tables (515 floats): coalesced loads that depend on nothing, no arithmetic.
-    // (Issuing a kernel's first tile loads before this copy, so that its latency runs under theirs, measured no faster.)
+    // a plain copy of the compile-time tables (515 floats): coalesced loads that depend on nothing, no arithmetic
     const int t = (int)threadIdx.x;
     const float a = kScaleTablesInit.v[t], b = kScaleTablesInit.v[256 + t];
     const float c = kScaleTablesInit.v[t < kScaleTables - 512 ? 512 + t : 512];

@@ -777,7 +777,8 @@ extern "C" int fcv2_dispatch_quant_noalloc(const void* x, const int32_t* ids, ui
     void* ws = scratch_of_current_device();
     if (!ws) return FCV2_ERR_LAUNCH;
     // Nothing in the scratch has to start at zero: the counting kernel writes every histogram entry of every chunk, the
-    // scan every total, the rank kernel every destination slot, before any of them is read.
+    // scan or the ranking kernel every total, k_dispatch_dest every destination row, before any of them is read.  The ranks
+    // (of either kernel) are written for routed slots only; what the row kernel reads in a dropped slot's place it does not use.
     return fcv2::dispatch_checked(x, ids, T, H, K, E, fmt, send, expert_offsets, row_src, ws, FCV2_STATIC_SCRATCH_BYTES, false, stream);
 }
 

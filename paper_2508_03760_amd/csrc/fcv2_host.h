@@ -76,7 +76,7 @@ static DispatchWs dispatch_ws(uint32_t T, uint32_t K, uint32_t E) {
     w.off_hist = 0;                                                                 // [n_chunks][E] int32
     w.off_totals = round_up((size_t)w.n_chunks * E * 4, 256);                        // [E] int32
     w.off_lrank = w.off_totals + round_up((size_t)E * 4, 256);                       // [n_slots] bytes: rank inside the chunk
-    w.off_dest = w.off_lrank + round_up((size_t)w.n_slots, 256);                     // [n_slots] int32: only the direct kernel reads it
+    w.off_dest = w.off_lrank + round_up((size_t)w.n_slots, 256);                     // [n_slots] int32: rows for the direct kernel, or the ranks of k_dispatch_rank
     w.bytes = w.off_dest + round_up((size_t)w.n_slots * 4, 256);
     return w;
 }

@@ -198,7 +198,7 @@ __device__ __forceinline__ void add_peer_values(const RawPlanes<EPL>& r, const G
 // The sums of a wave's lanes, 64 bytes each, through the lanes' LDS rows into stores that cover whole lines: written from the lanes
 // directly, a store instruction would touch a quarter of each of 32 lines.
 // Measured on the MI355X (buffers not in the last-level cache, us per call, direct -> through LDS, with the non-temporal hint):
-// 3.2 M elements of 5 peers at 8 bits 11.2 -> 8.4, 16 M of 8 at 3 bits 43.3 -> 35.3, 16 M of 4 at 8 bits 41.0 -> 31.5.
+// 3.2 M elements of 5 peers at 8 bits 10.4 -> 6.7, 16 M of 8 at 3 bits 43.3 -> 35.3, 16 M of 4 at 8 bits 41.0 -> 31.5.
 template <int EPL, int ROW> __device__ __forceinline__ void store_sums(float* sum_out, uint4* lds, uint32_t L, uint32_t n_lanes, const float (&acc)[EPL]) {
     const uint32_t lane = threadIdx.x & 63, first = threadIdx.x - lane, L0 = L - lane;
     const uint32_t here = min(64u, n_lanes - L0);  // lanes of the wave that have elements: the first ones
